@@ -21,8 +21,8 @@
 // k_attn_bf16 (d = 64, more than 32 rows) and k_attn_bf16_groups (groups of at most
 // 32 rows: one wave per group, every wave streaming its own groups' tiles).
 //
-// f32 kernel (k_attn_f32): one lane per query row, fp32 dot products and exact
-// expf-based online softmax, for fp32 inputs.
+// f32 kernel (k_attn_f32): the same formulation on fp32 MFMA, the keys of a 32-row tile
+// split over the waves of its workgroup, for fp32 inputs.
 #include <limits.h>
 #include <math.h>
 #include <atomic>
@@ -55,53 +55,6 @@ struct AttnArgs {
   void* out;
   float* lse;
   int tiles_per_group;
-};
-
-// Walks the (block, sub-tile) sequence of a block list, skipping padding,
-// out-of-range ids and non-resident pages.  Everything here is workgroup-uniform.
-template <int TK>
-struct TileWalk {
-  const AttnArgs& a;
-  const int32_t* table;  // the head's page table
-  const int32_t* list;
-  int count;
-  int t = 0, sub = 0;
-  int64_t page = 0;
-  int nvalid = 0;
-
-  __device__ TileWalk(const AttnArgs& args, const int32_t* pt, const int32_t* l, int c)
-      : a(args), table(pt), list(l), count(c) {}
-
-  // position on the next non-empty tile at or after (t, sub); false at the end
-  __device__ bool seek() {
-    while (t < count) {
-      const int id = list ? list[t] : a.dense_first + t;
-      if (id >= 0 && id < a.nb) {
-        const int32_t p = table[id];
-        if (p >= 0 && p < a.num_pages) {
-          const int o = id % a.Bpc;
-          const int in_block = (o == a.Bpc - 1 ? a.S - o * a.B : a.B) - sub * TK;
-          if (in_block > 0) {
-            page = p;
-            nvalid = in_block < TK ? in_block : TK;
-            return true;
-          }
-        }
-      }
-      ++t;
-      sub = 0;
-    }
-    return false;
-  }
-  __device__ void advance() {
-    if (++sub * TK >= a.B) {
-      ++t;
-      sub = 0;
-    }
-  }
-  __device__ int64_t slab_offset(int h, int D) const {
-    return (page * a.H + h) * static_cast<int64_t>(a.B) * D + static_cast<int64_t>(sub) * TK * D;
-  }
 };
 
 __device__ __forceinline__ void resolve_tile(const AttnArgs& a, int rows_per_wg, int& h, int& hr, int& row0,
@@ -1295,71 +1248,231 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   }
 }
 
-// ------------------------------------------------------------------ fp32 / SIMT
+// ------------------------------------------------------------------ fp32 / MFMA
+// fp32 attention on v_mfma_f32_32x32x2_f32 (fp32 products and accumulation, 64 flops per
+// cycle and SIMD): S^T = K Q^T, O^T += V^T P^T, as in the bf16 kernels.  The MFMAs bound
+// it: a score costs 4 d flops, so the softmax is a twelfth of a tile's cycles at d = 128.
+//  - A workgroup is 32 query rows of one (head, group); its waves split the keys, wave w
+//    taking the 32-key tiles w, w + waves, ..., and meet in LDS at the end.  So the row
+//    tile stays small (a 1,560-row frame of 12 heads gives 588 workgroups, a 256-row one of
+//    2 heads 16 with their keys spread over every wave), no wave waits for another inside
+//    the loop, and two workgroups share a CU.
+//  - MFMA step (u, e) of the scores multiplies dimension 8 u + 4 half + e of both operands
+//    (any bijection will do, as long as K and Q agree), so a lane's K and Q come 16 bytes
+//    at a time.  K passes through the wave's own LDS tile: read from memory in the operand
+//    layout, 64 separate 16-byte pieces a load, the vector cache was busy 62% of the time
+//    and the frame below took 132 us instead of 117.
+//  - Accumulator element i of lane l is key 8 (i / 4) + 4 half + i % 4, query l % 32: PV step
+//    i takes P as it stands as the B operand and V rows 8 (i / 4) + 4 half + i % 4 as the
+//    A operand, lane l % 32 = c supplying d = DT c + dt to accumulator dt with one load.
+//  - K of the next tile is on its way while the PV MFMAs of this one run, V while the next
+//    tile's QK MFMAs run: one copy of each.
+// Against one lane per query row with its dot products and exponentials in series, at
+// 12 heads x 1,560 rows x 1,024 keys, d = 128: 2,485 -> 117 us (82 TFLOP/s; 62 us at the
+// rate of a large fp32 product, 82 us for the CUs that get three of the 588 workgroups);
+// at 2 heads x 256 rows x 256 keys, d = 64: 292 -> 11 us.
+constexpr int kF32Rows = 32;
 constexpr int kF32Keys = 32;
 
+// Waves per workgroup; 256 registers a wave allow two per SIMD.
 template <int D>
-__global__ __launch_bounds__(kWave) void k_attn_f32(AttnArgs a) {
-  __shared__ float k_lds[kF32Keys][D];
-  __shared__ float v_lds[kF32Keys][D];
+struct F32Shape {
+  static constexpr int NW = D == 128 ? 4 : 8;
+  static constexpr int STRIDE = D + 4;  // LDS row of O, in floats: 16 rows cover the banks once
+};
+
+template <int D>
+__global__ __launch_bounds__(F32Shape<D>::NW* kWave, 2) void k_attn_f32(AttnArgs a) {
+  constexpr int NW = F32Shape<D>::NW, STRIDE = F32Shape<D>::STRIDE;
+  constexpr int NT = NW * kWave;
+  constexpr int U = D / 8;    // 16-byte K pieces per lane and tile
+  constexpr int DT = D / 32;  // accumulators along d, floats per V load
+  typedef float vdt __attribute__((ext_vector_type(DT)));
+  __shared__ __attribute__((aligned(16))) float o_lds[NW * kF32Rows * STRIDE];
+  __shared__ float m_lds[NW][kF32Rows], l_lds[NW][kF32Rows];
+  __shared__ int2 table[2 * NT];
+  __shared__ int scan_tmp[NW];
+
   int h, hr, row0, row_end;
-  resolve_tile(a, kWave, h, hr, row0, row_end);
-  if (row0 >= row_end) return;
+  resolve_tile(a, kF32Rows, h, hr, row0, row_end);
+  if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
   const int32_t* list;
   int count;
   resolve_list(a, hr, list, count);
-  const int lane = threadIdx.x;
-  const int my_row = row0 + lane;
-  const bool active = my_row < row_end;
+  const int tid = threadIdx.x, lane = tid % kWave, half = lane / 32, col = lane % 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const float* qp = static_cast<const float*>(a.q);
   const float* kp = static_cast<const float*>(a.k_pages);
   const float* vp = static_cast<const float*>(a.v_pages);
 
-  float qv[D], o[D];
+  f32x4 q[U];
 #pragma unroll
-  for (int j = 0; j < D; ++j) {
-    qv[j] = active ? qp[(static_cast<int64_t>(my_row) * a.H + h) * D + j] : 0.f;
-    o[j] = 0.f;
+  for (int u = 0; u < U; ++u) {
+    q[u] = f32x4{};
+    if (row0 + col < row_end)
+      q[u] = *reinterpret_cast<const f32x4*>(qp + (static_cast<int64_t>(row0 + col) * a.H + h) * D + 8 * u + 4 * half);
   }
-  float m = -INFINITY, l = 0.f;
-  TileWalk<kF32Keys> walk(a, head_table(a, h), list, count);
-  while (walk.seek()) {
-    const float* ks = kp + walk.slab_offset(h, D);
-    const float* vs = vp + walk.slab_offset(h, D);
-    const int nvalid = walk.nvalid;
-    for (int i = lane; i < kF32Keys * D / 4; i += kWave) {
-      const int row = i / (D / 4), c4 = i % (D / 4);
-      float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-      if (row < nvalid) {
-        kv = *reinterpret_cast<const float4*>(ks + row * D + 4 * c4);
-        vv = *reinterpret_cast<const float4*>(vs + row * D + 4 * c4);
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16{};
+  float m_run = -INFINITY, l_run = 0.f;  // max of scale * <q, k>, this lane's share of l
+
+  vdt vr[16];
+  // Tile t of the table's 64-key entries halved: the element offset of its first key and
+  // its valid keys.
+  auto tile_of = [&](int t, int64_t& off) -> int {
+    const int2 e = table[t / 2];
+    const int page = __builtin_amdgcn_readfirstlane(e.x), meta = __builtin_amdgcn_readfirstlane(e.y);
+    const int s = t % 2;
+    off = ((static_cast<int64_t>(page) * a.H + h) * a.B + (meta >> 8) * kTileKeys + s * kF32Keys) * D;
+    const int nv = (meta & 255) - s * kF32Keys;
+    return nv < kF32Keys ? nv : kF32Keys;
+  };
+  // K and V are read through buffer descriptors that end at the tile's last valid key: rows
+  // past it read as zero, so what a page holds there never reaches a product.
+  // K goes to LDS by DMA: an instruction moves 1 KB of whole rows, lane l the 16-byte
+  // chunk that belongs at position l of it.  Chunk c of row r sits at position
+  // c ^ (r mod 16) of its row, so that the operand reads (one chunk of 16 consecutive
+  // rows a pass) touch every bank once.
+  constexpr int CPR = D / 4, RPI = kWave / CPR;  // chunks per row, rows per instruction
+  float* const k_lds = o_lds + wave * kF32Keys * D;
+  auto load_k = [&](int64_t off, int nv) {
+    const u32x4 rsrc = buffer_rsrc(kp + off, nv * D * 4);
+    int at = (lane / CPR) * D * 4 + (((lane % CPR) ^ (lane / CPR)) << 4);
+    uint32_t dst = lds_offset(k_lds);
+    asm volatile("" : "+v"(at), "+s"(dst));  // form the instructions' offsets here, not in registers across the loop
+#pragma unroll
+    for (int m = 0; m < kF32Keys / RPI; ++m)
+      dma_16x64(rsrc, (at ^ (((RPI * m) % 16) << 4)) + m * kWave * 16, dst + m * kWave * 16);
+  };
+  auto load_v = [&](int64_t off, int nv) {
+    const u32x4 r = buffer_rsrc(vp + off, nv * D * 4);
+    const auto rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(static_cast<uint64_t>(r[1]) << 32 | r[0]), 0, r[2], r[3]);
+    const int at = (4 * half * D + DT * col) * 4;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int from = at + (i % 4) * D * 4, group = 8 * (i / 4) * D * 4;
+      if constexpr (DT == 4) vr[i] = __builtin_bit_cast(vdt, __builtin_amdgcn_raw_buffer_load_b128(rsrc, from, group, 0));
+      else vr[i] = __builtin_bit_cast(vdt, __builtin_amdgcn_raw_buffer_load_b64(rsrc, from, group, 0));
+    }
+  };
+
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // Q has landed: no wait for it inside the loop
+  for (int first = 0; first < count; first += NT) {
+    const int ntiles =
+        2 * __builtin_amdgcn_readfirstlane(decode_tiles<NT>(a, head_table(a, h), list, count, first, table, scan_tmp));
+    // this wave's next tile with a valid key at or after t
+    int64_t off = 0;
+    auto seek = [&](int& t) -> int {
+      for (; t < ntiles; t += NW) {
+        const int nv = tile_of(t, off);
+        if (nv > 0) return nv;
       }
-      *reinterpret_cast<float4*>(&k_lds[row][4 * c4]) = kv;
-      *reinterpret_cast<float4*>(&v_lds[row][4 * c4]) = vv;
+      return 0;
+    };
+    int t = wave, nvalid = seek(t);
+    if (nvalid > 0) {
+      load_k(off, nvalid);
+      load_v(off, nvalid);
     }
-    __syncthreads();
-    for (int key = 0; key < nvalid; ++key) {
-      float dot = 0.f;
+    while (nvalid > 0) {
+      // K has landed when at most the 16 V loads issued after its DMA are outstanding
+      asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      f32x16 s0 = f32x16{};
+      int at = col * D * 4 + ((half ^ (col % 16)) << 4);  // chunk 2 u + half of row col: at ^ (u << 5)
+      asm volatile("" : "+v"(at));
 #pragma unroll
-      for (int j = 0; j < D; ++j) dot = fmaf(qv[j], k_lds[key][j], dot);
-      const float s = a.scale * dot;
-      const float m_new = fmaxf(m, s);
-      const float alpha = expf(m - m_new);
-      const float p = expf(s - m_new);
-      l = l * alpha + p;
+      for (int u = 0; u < U; ++u) {
+        const f32x4 k = *reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(k_lds) + (at ^ (u << 5)));
 #pragma unroll
-      for (int j = 0; j < D; ++j) o[j] = fmaf(p, v_lds[key][j], o[j] * alpha);
-      m = m_new;
+        for (int e = 0; e < 4; ++e) s0 = __builtin_amdgcn_mfma_f32_32x32x2f32(k[e], q[u][e], s0, 0, 0, 0);
+      }
+      t += NW;
+      const int next_valid = seek(t);
+      // V, in flight since the last PV run, has landed: said here, so that no later wait for it
+      // counts the DMA issued next
+      __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+      if (next_valid > 0) load_k(off, next_valid);
+      if (nvalid < kF32Keys) {  // the block's last tile: keys past its end count for nothing
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (8 * (i / 4) + 4 * half + i % 4 >= nvalid) s0[i] = -INFINITY;
+      }
+      float mx = s0[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s0[i]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * a.scale;
+      if (__any(mx > m_run)) {  // rescale only when some row's running max grows
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
+        l_run *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+        m_run = m_new;
+      }
+      const float m0 = m_run == -INFINITY ? 0.f : m_run;
+      // scale * s - max with one rounding, before the change to log2 units: the exponent's
+      // error is then relative to its distance from the max
+      float sum = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        s0[i] = __builtin_amdgcn_exp2f(fmaf(s0[i], a.scale, -m0) * kLog2e);
+        sum += s0[i];
+      }
+      l_run += sum;
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i][dt], s0[i], o[dt], 0, 0, 0);
+      if (next_valid > 0) load_v(off, next_valid);
+      nvalid = next_valid;
     }
-    __syncthreads();
-    walk.advance();
+    __syncthreads();  // every wave is done with the table
   }
-  if (!active) return;
-  float* op = static_cast<float*>(a.out) + (static_cast<int64_t>(my_row) * a.H + h) * D;
-  const float inv = l > 0.f ? 1.0f / l : 0.f;
+
+  // ---- the waves' partial results meet in LDS: O^T element (dt, i) is d = DT c + dt of
+  // c = 8 (i / 4) + 4 half + i % 4
+  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  if (half == 0) {
+    m_lds[wave][col] = m_run;
+    l_lds[wave][col] = l_tot;
+  }
+  float* mine = o_lds + (wave * kF32Rows + col) * STRIDE;
 #pragma unroll
-  for (int j = 0; j < D; ++j) op[j] = o[j] * inv;
-  if (a.lse) a.lse[static_cast<int64_t>(h) * a.lq + my_row] = l > 0.f ? m + logf(l) : -INFINITY;
+  for (int i = 0; i < 16; ++i) {
+    vdt w;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) w[dt] = o[dt][i];
+    *reinterpret_cast<vdt*>(mine + DT * (8 * (i / 4) + 4 * half + i % 4)) = w;
+  }
+  __syncthreads();
+  constexpr int C4 = D / 4;  // 16-byte pieces per output row
+  for (int i = tid; i < kF32Rows * C4; i += NT) {
+    const int r = i / C4, c4 = i % C4, row = row0 + r;
+    float m = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m = fmaxf(m, m_lds[w][r]);
+    float l = 0.f;
+    f32x4 acc = f32x4{};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float weight = m_lds[w][r] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_lds[w][r] - m) * kLog2e);
+      const f32x4 ow = *reinterpret_cast<const f32x4*>(o_lds + (w * kF32Rows + r) * STRIDE + 4 * c4);
+      l = fmaf(weight, l_lds[w][r], l);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(weight, ow[e], acc[e]);
+    }
+    if (row < row_end) {
+      const float inv = l > 0.f ? 1.0f / l : 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] *= inv;
+      *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + (static_cast<int64_t>(row) * a.H + h) * D + 4 * c4) = acc;
+      if (a.lse && c4 == 0) a.lse[static_cast<int64_t>(h) * a.lq + row] = l > 0.f ? m + logf(l) : -INFINITY;
+    }
+  }
 }
 
 // Workgroups of the one-wave-per-group kernel: one wave per group, at most as many
@@ -1417,7 +1530,7 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
   // bf16, d = 128 and groups of more than 32 rows: 64 rows per wave; else 32
   const bool r64 = g.dtype == 0 && g.D == 128 && rows > 32;
   const bool small = rows <= 32;  // one 32-row tile per group: a wave per group
-  const int rows_per_wg = g.dtype != 0 ? kWave : r64 ? kR64Waves * 64 : small ? 32 : kWaves * 32;
+  const int rows_per_wg = g.dtype != 0 ? kF32Rows : r64 ? kR64Waves * 64 : small ? 32 : kWaves * 32;
   a.tiles_per_group = (rows + rows_per_wg - 1) / rows_per_wg;
   const int64_t nwg = static_cast<int64_t>(g.H) * L.R * a.tiles_per_group;
   if (nwg <= 0) return hipSuccess;
@@ -1433,8 +1546,8 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
     return launch_kernel(k_attn_bf16_groups<64>, dim3(group_workgroups<64>(nwg)), dim3(kGrpWaves * kWave), 0, stream,
                          a);
   }
-  if (g.D == 128) return launch_kernel(k_attn_f32<128>, grid, dim3(kWave), 0, stream, a);
-  return launch_kernel(k_attn_f32<64>, grid, dim3(kWave), 0, stream, a);
+  if (g.D == 128) return launch_kernel(k_attn_f32<128>, grid, dim3(F32Shape<128>::NW * kWave), 0, stream, a);
+  return launch_kernel(k_attn_f32<64>, grid, dim3(F32Shape<64>::NW * kWave), 0, stream, a);
 }
 
 }  // namespace omnimem

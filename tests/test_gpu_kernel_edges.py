@@ -1,0 +1,88 @@
+"""Sizes where one kernel or one branch of a dispatch can go wrong: edges of tiles,
+remainders, the smallest and largest of a range, against the fp64 oracle.  The bars are
+those of parity.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2605_30519_amd import omnimem_dense_attn, omnimem_sparse_attn, synth
+from parity import check_bf16, check_f32, check_lse, say
+
+pytestmark = pytest.mark.gpu
+NAN = float("nan")
+
+
+@pytest.fixture(scope="module")
+def dev():
+    d = torch.device("cuda:0")
+    torch.cuda.set_device(d)
+    return d
+
+
+def make(dev, H, d, S, Lq, B, n, dtype, seed, nonresident=()):
+    g = torch.Generator().manual_seed(seed)
+    q = torch.randn(Lq, H, d, generator=g).to(dtype)
+    k = torch.randn(n, S, H, d, generator=g).to(dtype)
+    v = torch.randn(n, S, H, d, generator=g).to(dtype)
+    cache = synth.page_layer(k.to(dev), v.to(dev), B, seed=seed, pad_value=NAN, nonresident=nonresident)
+    return q, k, v, cache, synth.resident_mask(cache).numpy()
+
+
+def check(got, ref, dtype, what):
+    (out, lse), (o_ref, l_ref, hs, qs) = got, ref
+    o, l = out.cpu().float().numpy()[qs, hs], lse.cpu().numpy()[hs, qs]
+    (check_f32 if dtype == torch.float32 else check_bf16)(o, o_ref, what)
+    check_lse(l, l_ref, what + " lse", 1e-5 if dtype == torch.float32 else 5e-3)
+
+
+def random_lists(rng, H, R, K, nb):
+    """Lists of every length from none to K, with padding, an id past the end and
+    duplicates among their entries."""
+    idx = rng.integers(0, nb, (H, R, K)).astype(np.int32)
+    idx[rng.random((H, R, K)) < 0.1] = -1
+    idx[rng.random((H, R, K)) < 0.03] = nb
+    cnt = rng.integers(0, K + 1, (H, R)).astype(np.int32)
+    cnt[0, 0], cnt[-1, -1] = 0, K
+    return idx, cnt
+
+
+def sparse_ref(q, k, v, B, idx, cnt, G, scale, resident):
+    nb = k.shape[0] * -(-k.shape[1] // B)
+    idx = np.where(idx >= nb, -1, idx).astype(np.int32)   # the oracle refuses ids past the end; both skip padding
+    return oracle.sparse_attn(q, k, v, B, idx, cnt, G, scale, resident=resident)
+
+
+# fp32: 32-row tiles (one row, one short of a tile, one over), 32-key tiles (a tail of 1,
+# 32, 33 and 72 tokens), fewer key tiles than waves and more
+@pytest.mark.parametrize("H,d,S,Lq,B,n,K,G", [(2, 64, 65, 31, 64, 3, 2, 31), (2, 128, 161, 33, 64, 4, 5, 33),
+                                              (1, 128, 96, 1, 64, 2, 1, 1), (3, 64, 200, 130, 128, 5, 7, 65),
+                                              (2, 128, 200, 70, 128, 5, 9, 15), (1, 64, 128, 64, 64, 20, 30, 32)])
+def test_fp32_attention(dev, H, d, S, Lq, B, n, K, G):
+    say(f"fp32 attention H={H} d={d} S={S} Lq={Lq} B={B} n={n} K={K} G={G}")
+    q, k, v, cache, resident = make(dev, H, d, S, Lq, B, n, torch.float32, 3 * Lq + d, nonresident=[1])
+    idx, cnt = random_lists(np.random.default_rng(Lq), H, -(-Lq // G), K, n * -(-S // B))
+    qd, scale = q.to(dev), d ** -0.5
+    got = omnimem_sparse_attn(cache, qd, torch.from_numpy(idx).to(dev), torch.from_numpy(cnt).to(dev), G, scale)
+    check(got, sparse_ref(q, k, v, B, idx, cnt, G, scale, resident), torch.float32, "sparse")
+    got = omnimem_dense_attn(cache, qd, 0, n, scale)
+    check(got, oracle.dense_attn(q, k, v, B, 0, n, scale, resident=resident), torch.float32, "dense")
+
+
+@pytest.mark.parametrize("d,n", [(64, 513), (128, 257)])
+def test_fp32_attention_long(dev, d, n):
+    """Block lists longer than one decoded stretch (one entry per thread), and scores whose
+    running max jumps between blocks by hundreds."""
+    say(f"fp32 attention long d={d} n={n}")
+    q, k, v, _, _ = make(dev, 1, d, 64, 33, 64, n, torch.float32, n)
+    k[3::50] *= 30.0
+    cache = synth.page_layer(k.to(dev), v.to(dev), 64, seed=6)
+    got = omnimem_dense_attn(cache, q.to(dev), 0, n, d ** -0.5)
+    check_ref = oracle.dense_attn(q, k, v, 64, 0, n, d ** -0.5)
+    (out, lse), (o_ref, l_ref, hs, qs) = got, check_ref
+    # scores of up to ~150: their fp32 rounding (2^-24 relative) moves a probability by
+    # 150 * 6e-8 = 9e-6 of itself, and outputs of up to 5 by as much again
+    err = np.abs(out.cpu().numpy()[qs, hs] - o_ref).max()
+    say(f"  max-abs {err:.2e}")
+    assert err <= 1e-4
+    assert np.allclose(lse.cpu().numpy()[hs, qs], l_ref, rtol=2e-6, atol=1e-5)
