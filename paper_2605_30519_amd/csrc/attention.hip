@@ -2,11 +2,9 @@
 // the paged KV cache (Sec. 3.3 Eq. 5, Per-Head Scattered KV Access; App. C Alg. 1
 // Step 2), and over contiguous chunk ranges (dense / sliding-window attention).
 //
-// bf16 kernel (k_attn_bf16): flash-style, one workgroup = 4 waves = a tile of
-// query rows of one (head, query group); the group's block list is walked 64 keys
-// at a time.  Each 64-key tile of K and V (one (page, head) slab, or half of one at
-// B = 128) is staged in LDS with 16-byte coalesced loads, prefetched into registers
-// one tile ahead.  Every wave keeps 32 query rows of Q in registers and computes
+// bf16 kernels: flash-style, a group's block list walked 64 keys at a time (one
+// (page, head) slab, or half of one at B = 128).  A wave keeps 32-row tiles of Q in
+// registers and computes, for each,
 //   S^T = K Q^T        on v_mfma_f32_32x32x16_bf16 (K rows as the A operand),
 //   O^T += V^T P^T     on the same instruction, V^T read with ds_read_b64_tr_b16,
 // so that each lane owns one query column of both S^T and O^T: the online softmax
@@ -16,10 +14,10 @@
 // S^T accumulator registers line up with the B-operand layout of P^T, so P goes from
 // accumulator to MFMA operand with a bf16 pack and nothing else.
 //
-// The same arithmetic runs in three data-movement shapes: k_attn_bf16_r64 (d = 128,
-// groups of more than 32 rows: 64 rows per wave, tiles by buffer-to-LDS DMA),
-// k_attn_bf16 (d = 64, more than 32 rows) and k_attn_bf16_groups (groups of at most
-// 32 rows: one wave per group, every wave streaming its own groups' tiles).
+// The same arithmetic runs in two data-movement shapes: k_attn_bf16_r64 (groups of more
+// than 32 rows: 64 rows per wave, tiles by buffer-to-LDS DMA, the keys split over sets of
+// waves where the grid is small) and k_attn_bf16_groups (groups of at most 32 rows: one
+// wave per group, every wave streaming its own groups' tiles).
 //
 // f32 kernel (k_attn_f32): the same formulation on fp32 MFMA, the keys of a 32-row tile
 // split over the waves of its workgroup, for fp32 inputs.
@@ -120,264 +118,18 @@ __device__ int decode_tiles(const AttnArgs& a, const int32_t* pt, const int32_t*
 }
 
 // ------------------------------------------------------------------ bf16 / MFMA
-constexpr int kWaves = 8;  // 256 query rows per workgroup, two waves per SIMD
-
 // A-operand row order for S^T = K Q^T: swapping bits 2 and 3 of the row makes the
 // accumulator element i of lane l hold key 8*(l/32)+i (i < 8) or 16+8*(l/32)+(i-8).
 __device__ __forceinline__ int s_row_perm(int x) { return (x & ~12) | ((x & 4) << 1) | ((x & 8) >> 1); }
 
-// LDS row strides (bf16 elements), chosen for gfx950's 64 four-byte banks:
-//  K rows are read 16 B per lane, 16 lanes (16 rows) per pass: a stride of 4 (mod 64)
-//    dwords puts the 16 rows on disjoint bank quads;
-//  V rows are read by ds_read_b64_tr_b16, 4 rows x 32 B per 16-lane group and two
-//    groups per pass: a stride of 16 or 48 (mod 64) dwords makes the 8 row segments of a
-//    pass disjoint.
+// LDS row stride of a V tile (bf16 elements), chosen for gfx950's 64 four-byte banks: V
+// rows are read by ds_read_b64_tr_b16, 4 rows x 32 B per 16-lane group and two groups per
+// pass: a stride of 16 or 48 (mod 64) dwords makes the 8 row segments of a pass disjoint.
 template <int D>
 struct AttnLds {
-  static constexpr int K_STRIDE = D == 128 ? 136 : 72;
   static constexpr int V_STRIDE = D == 128 ? 160 : 96;
-  static constexpr int K_ELEMS = kTileKeys * K_STRIDE;
   static constexpr int V_ELEMS = kTileKeys * V_STRIDE;
-  static constexpr int K_STAGES = 2;
-  static constexpr int V_STAGES = 3;  // the phase-shifted waves still read the previous tile's V
-  static constexpr int TOTAL_ELEMS = K_STAGES * K_ELEMS + V_STAGES * V_ELEMS;
 };
-
-// NW waves of 32 query rows, the upper half of the waves running half a tile behind
-// the lower half (see below); for d = 64 and groups of more than 32 rows.
-template <int D, int NW>
-__global__ __launch_bounds__(NW* kWave) void k_attn_bf16(AttnArgs a) {
-  using L = AttnLds<D>;
-  constexpr int NT = NW * kWave;
-  constexpr int ROWS = NW * 32;
-  constexpr int CHUNKS_PER_ROW = D / 8;                        // 16-byte chunks per key row
-  constexpr int CPT = kTileKeys * CHUNKS_PER_ROW / NT;         // chunks per thread per tile (K and V each)
-  constexpr int DT = D / 32;                                   // 32-wide output tiles along d
-  constexpr int KK = D / 16;                                   // k-steps of QK^T
-  static_assert(CPT >= 1, "tile too small for the workgroup");
-  __shared__ __attribute__((aligned(16))) uint16_t lds[L::TOTAL_ELEMS];
-  __shared__ int2 table[2 * NT];  // decoded tiles of up to NT list entries
-  __shared__ int scan_tmp[NW];
-  uint16_t* const k_ring = lds;
-  uint16_t* const v_ring = lds + L::K_STAGES * L::K_ELEMS;
-
-  int h, hr, row0, row_end;
-  resolve_tile(a, ROWS, h, hr, row0, row_end);
-  if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
-  const int32_t* list;
-  int count;
-  resolve_list(a, hr, list, count);
-
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
-  const int half = lane / 32;
-  const uint16_t* qp = static_cast<const uint16_t*>(a.q);
-  const uint16_t* kp = static_cast<const uint16_t*>(a.k_pages);
-  const uint16_t* vp = static_cast<const uint16_t*>(a.v_pages);
-
-  // Q^T as the B operand: lane holds query (lane % 32), d = 16*kk + 8*half + 0..7
-  const int my_row = row0 + wave * 32 + lane % 32;
-  const bool wave_live = row0 + wave * 32 < row_end;  // wave-uniform
-  bf16x8 qreg[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (my_row < row_end)
-      raw = *reinterpret_cast<const uint4*>(qp + (static_cast<int64_t>(my_row) * a.H + h) * D + 16 * kk + 8 * half);
-    qreg[kk] = __builtin_bit_cast(bf16x8, raw);
-  }
-
-  f32x16 o_acc[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o_acc[dt][i] = 0.f;
-  // running max (raw score units) and this lane's share of the denominator
-  float m_run = -INFINITY, l_run = 0.f;
-  const float c = a.scale * kLog2e;
-
-  uint4 kreg[CPT], vreg[CPT];
-  // loads one tile (page, sub-tile, valid keys) into the staging registers
-  auto prefetch = [&](int page, int meta) {
-    const int sub = meta >> 8, nv = meta & 255;
-    const int64_t slab = (static_cast<int64_t>(page) * a.H + h) * a.B * D + static_cast<int64_t>(sub) * kTileKeys * D;
-    const uint16_t* ks = kp + slab;
-    const uint16_t* vs = vp + slab;
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int cid = tid + i * NT;
-      const int row = cid / CHUNKS_PER_ROW, c8 = cid % CHUNKS_PER_ROW;
-      if (row < nv) {
-        kreg[i] = *reinterpret_cast<const uint4*>(ks + row * D + c8 * 8);
-        vreg[i] = *reinterpret_cast<const uint4*>(vs + row * D + c8 * 8);
-      } else {
-        kreg[i] = make_uint4(0, 0, 0, 0);
-        vreg[i] = make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  auto stage = [&](int kst, int vst) {
-#pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      const int cid = tid + i * NT;
-      const int row = cid / CHUNKS_PER_ROW, c8 = cid % CHUNKS_PER_ROW;
-      *reinterpret_cast<uint4*>(k_ring + kst * L::K_ELEMS + row * L::K_STRIDE + c8 * 8) = kreg[i];
-      *reinterpret_cast<uint4*>(v_ring + vst * L::V_ELEMS + row * L::V_STRIDE + c8 * 8) = vreg[i];
-    }
-  };
-
-  // The two waves that share a SIMD (w and w + 4) run the same tile half a step
-  // apart: waves 0-3 do QK(t), softmax(t), PV(t); waves 4-7 do PV(t-1), QK(t),
-  // softmax(t).  While one of them is in its softmax (VALU) the other issues MFMAs.
-  const bool late = wave >= NW / 2;
-  bf16x8 pb[4];
-  auto pv = [&](const uint16_t* v_lds) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int key0 = 16 * j + 8 * half + (lane % 16) / 4;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const int col = 32 * dt + 16 * ((lane / 16) % 2) + 4 * (lane % 4);
-        typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(v_lds + key0 * L::V_STRIDE + col));
-        const i16x4 hi =
-            __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(v_lds + (key0 + 4) * L::V_STRIDE + col));
-        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        o_acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pb[j], o_acc[dt], 0, 0, 0);
-      }
-    }
-  };
-
-  // tile table: decode list entries NT at a time; `ti` indexes the current table
-  int next_entry = 0, ntab = 0, ti = 0;
-  while (ntab == 0 && next_entry < count) {
-    ntab = decode_tiles<NT>(a, head_table(a, h), list, count, next_entry, table, scan_tmp);
-    next_entry += NT;
-  }
-  bool have = ntab > 0;
-  int2 cur_tile = have ? table[0] : make_int2(0, 0);
-  cur_tile.x = __builtin_amdgcn_readfirstlane(cur_tile.x);
-  cur_tile.y = __builtin_amdgcn_readfirstlane(cur_tile.y);
-  if (have) {
-    prefetch(cur_tile.x, cur_tile.y);
-    stage(0, 0);
-  }
-  __syncthreads();
-  const int krow = s_row_perm(lane % 32);
-  int t = 0;
-  while (have) {
-    const int cur_nvalid = cur_tile.y & 255;
-    if (++ti == ntab) {  // table exhausted: decode the next list entries (dense lists only)
-      ntab = 0;
-      ti = 0;
-      while (ntab == 0 && next_entry < count) {
-        ntab = decode_tiles<NT>(a, head_table(a, h), list, count, next_entry, table, scan_tmp);
-        next_entry += NT;
-      }
-    }
-    have = ti < ntab;
-    if (have) {
-      cur_tile = table[ti];
-      cur_tile.x = __builtin_amdgcn_readfirstlane(cur_tile.x);
-      cur_tile.y = __builtin_amdgcn_readfirstlane(cur_tile.y);
-      prefetch(cur_tile.x, cur_tile.y);  // next tile: global loads in flight during this tile's math
-    }
-    const uint16_t* k_lds = k_ring + (t % 2) * L::K_ELEMS;
-    const uint16_t* v_lds = v_ring + (t % L::V_STAGES) * L::V_ELEMS;
-
-    if (wave_live) {
-      if (late && t > 0) pv(v_ring + ((t + L::V_STAGES - 1) % L::V_STAGES) * L::V_ELEMS);  // PV of the previous tile
-      // ---- S^T = K Q^T for keys [0, 64): two 32-key accumulators
-      f32x16 s_acc[2];
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s_acc[t2][i] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const bf16x8 kf =
-              *reinterpret_cast<const bf16x8*>(k_lds + (32 * t2 + krow) * L::K_STRIDE + 16 * kk + 8 * half);
-          s_acc[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qreg[kk], s_acc[t2], 0, 0, 0);
-        }
-      }
-      // ---- online softmax for this lane's query (exp2 domain, scale folded into one FMA)
-      if (cur_nvalid < kTileKeys) {  // partial tile: mask the keys past the block's end
-#pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = 32 * t2 + (i < 8 ? 8 * half + i : 16 + 8 * half + (i - 8));
-            if (key >= cur_nvalid) s_acc[t2][i] = -INFINITY;
-          }
-      }
-      float mloc = s_acc[0][0];
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mloc = fmaxf(mloc, s_acc[t2][i]);
-      const float m_tile = fmaxf(mloc, __shfl_xor(mloc, 32));
-      // rescale only when some lane's running max grows (exact: alpha == 1 otherwise)
-      if (__any(m_tile > m_run)) {
-        const float m_new = fmaxf(m_run, m_tile);
-        const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * c);
-        l_run *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) o_acc[dt][i] *= alpha;
-        m_run = m_new;
-      }
-      const float mc = m_run == -INFINITY ? 0.f : m_run * c;
-      float psum = 0.f;
-#pragma unroll
-      for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s_acc[t2][i], c, -mc));
-          psum += p;
-          pb[2 * t2 + i / 8][i % 8] = static_cast<__bf16>(p);
-        }
-      l_run += psum;
-      if (!late) pv(v_lds);
-    }
-    if (have) stage((t + 1) % 2, (t + 1) % L::V_STAGES);  // stages not read in this step
-    __syncthreads();
-    ++t;
-  }
-  if (late && wave_live && t > 0) pv(v_ring + ((t + L::V_STAGES - 1) % L::V_STAGES) * L::V_ELEMS);  // the last tile's PV
-  __syncthreads();  // the rings are reused below for the output
-
-  // ---- epilogue: normalise, stage O through LDS, store rows with 16-byte writes
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  constexpr int SSTRIDE = D + 8;
-  static_assert(NW * 32 * SSTRIDE <= L::TOTAL_ELEMS, "output staging does not fit");
-  uint16_t* stage_o = lds + wave * 32 * SSTRIDE;
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int d0 = 32 * dt + 8 * i4 + 4 * half;
-      bf16x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(o_acc[dt][4 * i4 + e] * inv);
-      *reinterpret_cast<bf16x4*>(stage_o + (lane % 32) * SSTRIDE + d0) = w;
-    }
-  __syncthreads();
-  uint16_t* op = static_cast<uint16_t*>(a.out);
-  constexpr int OCHUNKS = 32 * CHUNKS_PER_ROW;
-#pragma unroll
-  for (int i = 0; i < OCHUNKS / kWave; ++i) {
-    const int cid = lane + i * kWave;
-    const int row = cid / CHUNKS_PER_ROW, c8 = cid % CHUNKS_PER_ROW;
-    const int qrow = row0 + wave * 32 + row;
-    if (qrow < row_end)
-      *reinterpret_cast<uint4*>(op + (static_cast<int64_t>(qrow) * a.H + h) * D + c8 * 8) =
-          *reinterpret_cast<const uint4*>(stage_o + row * SSTRIDE + c8 * 8);
-  }
-  if (a.lse && lane < 32 && my_row < row_end)
-    a.lse[static_cast<int64_t>(h) * a.lq + my_row] =
-        l_tot > 0.f ? (m_run * c + __log2f(l_tot)) * kLn2 : -INFINITY;
-}
 
 // ------------------------------------------------------------------ bf16 / MFMA, one wave per query group
 // Query groups of at most 32 rows (the small-group setting of App. B, where every
@@ -390,7 +142,7 @@ __global__ __launch_bounds__(NW* kWave) void k_attn_bf16(AttnArgs a) {
 // goes from memory straight into registers in the MFMA A-operand layout; V passes
 // through the wave's own LDS tile for the transposing reads.  The next group's list
 // entries are fetched when the walk enters a group, its Q rows with its first tile.
-// The arithmetic is that of the 32-row kernel: the same operand layouts, the same
+// The arithmetic is that of the 64-row kernel: the same operand layouts, an
 // online softmax, the same rounding.
 constexpr int kGrpWaves = 4;
 
@@ -683,7 +435,7 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
 // ------------------------------------------------------------------ bf16 / MFMA, 64 rows per wave
 // Four waves (one per SIMD) x 64 query rows, as two 32-row halves that share every
 // K and V operand read from LDS: each 1 KB operand fragment feeds two MFMAs, half the
-// LDS bytes per flop of the 32-row kernel, whose operand traffic equals the LDS
+// LDS bytes per flop of 32 rows per wave, whose operand traffic equals the LDS
 // bandwidth at the MFMA peak.  With one wave per SIMD the matrix core is kept busy
 // from inside the wave: the instruction stream alternates MFMAs of one half with
 // the softmax VALU work of the other (QK of half 1 with the exponentials of half
@@ -724,17 +476,28 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// LDS tiles of the 64-row kernel: 64 rows of 256 bytes (d = 128 bf16), unpadded, with
-// the 16-byte chunks of each row permuted so that both the K fragment reads and the
-// transposing V reads touch every bank once per pass:
-//   K: chunk c of row r sits at chunk position c ^ (r mod 16)
-//   V: chunk c of row r sits at chunk position c ^ 4 (r mod 4)
+// LDS tiles of the 64-row kernel: 64 rows of 2 d bytes, unpadded, with the 16-byte
+// chunks of each row permuted so that both the K fragment reads (one chunk of 16 rows a
+// pass) and the transposing V reads (4 chunks of 4 rows a pass) touch every bank once:
+//   K: chunk c of row r sits at chunk position c ^ (r mod 16), for d = 64, where two rows
+//      span the banks, at c ^ (r / 2 mod 8)
+//   V: at c ^ 4 (r mod 4), for d = 64 at c ^ 4 (r / 2 mod 2)
 // Tiles arrive by buffer-to-LDS DMA: one instruction moves 64 lanes x 16 bytes into a
-// contiguous 1 KB (rows 4m .. 4m + 3), lane l filling chunk position l mod 16 of row
-// 4m + l / 16, so each lane fetches the global chunk that belongs at its position.
-constexpr int kR64TileBytes = kTileKeys * 128 * 2;
-__device__ __forceinline__ int k_pos(int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); }
-__device__ __forceinline__ int v_pos(int r, int c) { return r * 256 + ((c ^ (4 * (r & 3))) << 4); }
+// contiguous 1 KB (4 rows, for d = 64 8), lane l filling position l mod (d / 8) of its
+// row, so each lane fetches the global chunk that belongs at its position.
+template <int D>
+struct R64Lds {
+  static constexpr int ROW = D * 2;                 // bytes per row
+  static constexpr int TILE = kTileKeys * ROW;      // bytes per tile, K or V
+  static constexpr int CHUNKS = D / 8;              // 16-byte chunks per row
+  static constexpr int DMA_ROWS = 1024 / ROW;       // rows per DMA instruction
+  __device__ __forceinline__ static int k_pos(int r, int c) {
+    return r * ROW + ((c ^ (D == 128 ? r & 15 : (r >> 1) & 7)) << 4);
+  }
+  __device__ __forceinline__ static int v_pos(int r, int c) {
+    return r * ROW + ((c ^ (D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1))) << 4);
+  }
+};
 
 // s_waitcnt operand that waits for at most n outstanding vector-memory operations
 // and for nothing else (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
@@ -774,6 +537,9 @@ __device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16
 __device__ __forceinline__ void acc_settled(f32x16 (&o)[4]) {
   asm volatile("s_nop 7\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
 }
+__device__ __forceinline__ void acc_settled(f32x16 (&o)[2]) {
+  asm volatile("s_nop 7\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]));
+}
 
 
 // One buffer-to-LDS DMA instruction: lane l's 16 bytes at rsrc + voffset land at LDS
@@ -787,21 +553,29 @@ __device__ __forceinline__ void dma_16x64(u32x4 rsrc, int voffset, uint32_t lds)
   asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(rsrc), "{m0}"(lds) : "memory");
 }
 
-template <int D>
+// KS key streams: the workgroup's waves are KS sets of 4 / KS row waves, set j walking
+// tiles j, j + KS, ... of the list and the sets meeting in LDS at the end, for grids that
+// would leave CUs idle with 256 rows per workgroup.
+template <int D, int KS>
 __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs a) {
-  static_assert(D == 128, "the 64-row kernel is laid out for d = 128");
+  using L = R64Lds<D>;
   constexpr int NT = kR64Waves * kWave;
-  constexpr int ROWS = kR64Waves * 64;
+  constexpr int RW = kR64Waves / KS;  // row waves per stream
+  constexpr int ROWS = RW * 64;
   constexpr int DT = D / 32;
   constexpr int KK = D / 16;
-  constexpr int DMA_PER_WAVE = kR64TileBytes / 1024 / kR64Waves;  // 1 KB DMA instructions per wave, K and V each
-  // Four stages of K and V, tile t in stage t mod 4: iteration t reads the K of tile t
-  // and the V of tile t - 1 while tile t + 1 has landed and tile t + 2 arrives in the
-  // stage of tile t - 2.
-  constexpr int kStages = 4;
-  __shared__ __attribute__((aligned(1024))) uint8_t k_ring[kStages * kR64TileBytes];
-  __shared__ __attribute__((aligned(1024))) uint8_t v_ring[kStages * kR64TileBytes];
-  __shared__ int2 table[2 * NT];
+  constexpr int DMA_PER_WAVE = L::TILE / 1024 / RW;  // 1 KB DMA instructions per wave and tile, K and V each
+  // Four stages of K and V per stream where 128 KB hold them, tile t in stage t mod 4:
+  // iteration t reads the K of tile t and the V of tile t - 1 while tile t + 1 has landed
+  // and tile t + 2 arrives in the stage of tile t - 2.
+  // Else two: iteration t reads the K of tile t and the V of tile t - 1 while the K of
+  // tile t + 1 and the V of tile t arrive in the stages that iteration t - 1 has read.
+  constexpr bool kDeep = KS * 4 * 2 * L::TILE <= 131072;
+  constexpr int kStages = kDeep ? 4 : 2;
+  constexpr int kRing = KS * kStages * L::TILE;
+  __shared__ __attribute__((aligned(1024))) uint8_t k_ring[kRing];
+  __shared__ __attribute__((aligned(1024))) uint8_t v_ring[kRing];
+  __shared__ __attribute__((aligned(16))) int2 table[2 * NT];
   __shared__ int scan_tmp[kR64Waves];
 
   int h, hr, row0, row_end;
@@ -812,6 +586,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   resolve_list(a, hr, list, count);
 
   const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+  const int wave_r = KS == 1 ? wave : wave % RW, stream = KS == 1 ? 0 : wave / RW;
   // this thread's entry of the first decoded stretch, read without waiting for the
   // count (the list holds top_k entries)
   const int id0 = list != nullptr && tid < a.top_k ? list[tid] : INT_MIN;
@@ -822,7 +597,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
 
   // Q^T B operands of the two halves: lane holds query wrow + 32 g + lane % 32
   const float c = a.scale * kLog2e;  // scores to the softmax's log2 units, applied in fp32
-  const int wrow = row0 + wave * 64;
+  const int wrow = row0 + wave_r * 64;
   const bool wave_live = wrow < row_end;  // wave-uniform
   // the Q rows are loaded here and moved to AccVGPRs once the first tiles' DMA is
   // issued, so that their latency overlaps the block-list decode
@@ -854,8 +629,11 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // The next table entry as read from LDS (the same in every lane; made scalar where
   // used, so that the read's latency is not waited for here).  Called by every thread
   // together: it refills the table (with barriers) when it runs out.
+  // With several streams every stream takes its own of the next KS entries (an empty tile
+  // past the table's end), and `more` tells whether there was one for any of them.
+  bool more = false;
   auto next_tile_raw = [&]() -> int2 {
-    if (ti == ntab) {
+    if (KS == 1 ? ti == ntab : ti >= ntab) {
       ntab = 0;
       ti = 0;
       while (ntab == 0 && next_entry < count) {
@@ -863,46 +641,55 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
                                 next_entry == 0 ? id0 : INT_MIN);
         next_entry += NT;
       }
-      if (ntab == 0) return make_int2(0, 0);  // past the end: an empty tile
+      if (KS > 1) ntab = __builtin_amdgcn_readfirstlane(ntab);
+      if (ntab == 0) {  // past the end: an empty tile
+        more = false;
+        return make_int2(0, 0);
+      }
     }
-    return table[ti++];
+    if constexpr (KS == 1) return table[ti++];
+    more = true;
+    const int2 m = ti + stream < ntab ? table[ti + stream] : make_int2(0, 0);
+    ti += KS;
+    return m;
   };
   auto scalar_tile = [](int2 m) {
     return make_int2(__builtin_amdgcn_readfirstlane(m.x), __builtin_amdgcn_readfirstlane(m.y));
   };
-  // this lane's source offsets for its DMA instructions (row 4 m + lane / 16, m = wave + 4 i)
+  // this lane's source offsets for its DMA instructions (instruction m = wave_r + RW i of the tile)
   int k_src[DMA_PER_WAVE], v_src[DMA_PER_WAVE];
 #pragma unroll
   for (int i = 0; i < DMA_PER_WAVE; ++i) {
-    const int r = 4 * (wave + kR64Waves * i) + lane / 16, p = lane % 16;
-    k_src[i] = r * 256 + ((p ^ (r & 15)) << 4);
-    v_src[i] = r * 256 + ((p ^ (4 * (r & 3))) << 4);
+    const int r = L::DMA_ROWS * (wave_r + RW * i) + lane / L::CHUNKS, p = lane % L::CHUNKS;
+    k_src[i] = L::k_pos(r, p);
+    v_src[i] = L::v_pos(r, p);
   }
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // scalar copy: LDS destinations go to M0
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave_r);  // scalar copies: LDS destinations go to M0
+  const int ring0 = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(stream) * kStages * L::TILE;  // this stream's stages
   // Scalar bases: this head's slab of page 0, the page stride, and the wave's first
   // LDS destination.  Everything about a tile's DMA is then a few scalar ops.
   const int64_t h_elems = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(h)) * a.B * D;
   const uint16_t* const kp_h = kp + h_elems;
   const uint16_t* const vp_h = vp + h_elems;
   const int64_t page_elems = static_cast<int64_t>(a.H) * a.B * D;
-  const uint32_t m0_k = lds_offset(k_ring) + wave_s * 1024, m0_v = lds_offset(v_ring) + wave_s * 1024;
-  // the DMA of tile m into stage st, instruction i of K and of V (empty tiles load
-  // nothing and write zeros); m is workgroup-uniform.  The LDS bases pass through an
-  // empty asm so that each destination is formed where it is used: hoisted out of
-  // the loop, the 32 stage/instruction combinations would each hold a scalar register.
-  auto issue_part = [&](int2 m, int st, int i) {
-    const int sub = m.y >> 8, nv = m.y & 255;
-    const int64_t slab = static_cast<int64_t>(m.x) * page_elems + static_cast<int64_t>(sub) * kTileKeys * D;
-    const u32x4 kr = buffer_rsrc(kp_h + slab, nv * D * 2), vr = buffer_rsrc(vp_h + slab, nv * D * 2);
-    uint32_t mk = m0_k, mv = m0_v;
-    asm volatile("" : "+s"(mk), "+s"(mv));
-    const uint32_t off = st * kR64TileBytes + kR64Waves * i * 1024;
-    dma_16x64(kr, k_src[i], mk + off);
-    dma_16x64(vr, v_src[i], mv + off);
+  const uint32_t m0_k = lds_offset(k_ring) + ring0 + wave_s * 1024, m0_v = lds_offset(v_ring) + ring0 + wave_s * 1024;
+  auto slab_of = [&](int2 m) { return static_cast<int64_t>(m.x) * page_elems + static_cast<int64_t>(m.y >> 8) * kTileKeys * D; };
+  // instruction i of the DMA of tile mk's K into stage sk and of tile mv's V into stage sv
+  // (empty tiles load nothing and write zeros); the tiles are the same in every lane.  The
+  // LDS bases pass through an empty asm so that each destination is formed where it is
+  // used: hoisted out of the loop, the 32 stage/instruction combinations would each hold
+  // a scalar register.
+  auto issue_part = [&](int2 mk, int sk, int2 mv, int sv, int i) {
+    const u32x4 kr = buffer_rsrc(kp_h + slab_of(mk), (mk.y & 255) * D * 2),
+                vr = buffer_rsrc(vp_h + slab_of(mv), (mv.y & 255) * D * 2);
+    uint32_t dk = m0_k, dv = m0_v;
+    asm volatile("" : "+s"(dk), "+s"(dv));
+    dma_16x64(kr, k_src[i], dk + sk * L::TILE + RW * i * 1024);
+    dma_16x64(vr, v_src[i], dv + sv * L::TILE + RW * i * 1024);
   };
-  auto issue = [&](int2 m, int st) {
+  auto issue = [&](int2 mk, int sk, int2 mv, int sv) {
 #pragma unroll
-    for (int i = 0; i < DMA_PER_WAVE; ++i) issue_part(m, st, i);
+    for (int i = 0; i < DMA_PER_WAVE; ++i) issue_part(mk, sk, mv, sv, i);
   };
 
   // keys past the block's end of a partial tile get -inf scores (the key base goes
@@ -963,22 +750,22 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // base + constant cannot wrap)
   uint32_t k_lane[KK], v_lane[DT];
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) k_lane[kk] = (lds_offset(k_ring) + k_pos(krow, 2 * kk + half)) & 0x3ffffu;
+  for (int kk = 0; kk < KK; ++kk) k_lane[kk] = (lds_offset(k_ring) + ring0 + L::k_pos(krow, 2 * kk + half)) & 0x3ffffu;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) {
     const int key0 = 8 * half + (lane % 16) / 4;
     const int ch = 4 * dt + 2 * ((lane / 16) % 2) + (lane % 4) / 2;
-    v_lane[dt] = (lds_offset(v_ring) + v_pos(key0, ch) + 8 * (lane % 2)) & 0x3ffffu;
+    v_lane[dt] = (lds_offset(v_ring) + ring0 + L::v_pos(key0, ch) + 8 * (lane % 2)) & 0x3ffffu;
   }
   typedef __attribute__((address_space(3))) const uint8_t lds_u8;
   auto k_frag = [&](int st, int f) {  // f = 8 t2 + kk: keys 32 t2 .., k-step kk
-    lds_u8* p = reinterpret_cast<lds_u8*>(static_cast<uintptr_t>(k_lane[f % KK])) + (st * kR64TileBytes + (f / KK) * 32 * 256);
+    lds_u8* p = reinterpret_cast<lds_u8*>(static_cast<uintptr_t>(k_lane[f % KK])) + (st * L::TILE + (f / KK) * 32 * L::ROW);
     return *reinterpret_cast<__attribute__((address_space(3))) const bf16x8*>(p);
   };
   auto v_frag = [&](int st, int f) {  // f = 4 j + dt: keys 16 j .., d 32 dt ..; two transposing reads (keys +4)
-    lds_u8* p = reinterpret_cast<lds_u8*>(static_cast<uintptr_t>(v_lane[f % DT])) + (st * kR64TileBytes + (f / DT) * 16 * 256);
+    lds_u8* p = reinterpret_cast<lds_u8*>(static_cast<uintptr_t>(v_lane[f % DT])) + (st * L::TILE + (f / DT) * 16 * L::ROW);
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 4 * 256));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 4 * L::ROW));
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   // The exponentials of a half are computed against its running max before the
@@ -988,15 +775,28 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // formed again from the K still in LDS (stage kst, nvalid keys), its max taken, O
   // and l moved to the new max and the exponentials redone.  The next tile's
   // exponentials are formed after this point, against the new max.  The rare path is
-  // laid out away from the loop, which then runs straight through.
+  // laid out away from the loop, which then runs straight through.  With two stages the
+  // tile's K is already being replaced: it is read from memory again, in the operand
+  // layout (tile m; rows past its valid keys read as zero).
   auto settle = [&](float& ms, float& l, float acc, f32x16 (&o)[DT], bf16x8 (&pb)[4], const bf16x8 (&q)[KK], int kst,
-                    int nvalid) {
+                    int2 m) {
     if (__builtin_expect(__any(acc > kSlackSum), 0)) {
+      const int nvalid = m.y & 255;
+      const u32x4 r = buffer_rsrc(kp_h + slab_of(m), nvalid * D * 2);
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(
+          reinterpret_cast<void*>(static_cast<uint64_t>(r[1]) << 32 | r[0]), 0, r[2], r[3]);
+      int at = krow * L::ROW + 16 * half;
+      asm volatile("" : "+v"(at));
       f32x16 s[2];
 #pragma unroll
       for (int f = 0; f < 2 * KK; ++f) {
-        s[f / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_frag(kst, f), q[f % KK], f % KK ? s[f / KK] : f32x16{}, 0,
-                                                           0, 0);
+        bf16x8 k;
+        if constexpr (kDeep)
+          k = k_frag(kst, f);
+        else
+          k = __builtin_bit_cast(
+              bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at + 32 * (f % KK), (f / KK) * 32 * L::ROW, 0));
+        s[f / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q[f % KK], f % KK ? s[f / KK] : f32x16{}, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);  // one fragment at a time: this path must not raise register use
       }
       if (nvalid < kTileKeys) mask_tail(s, nvalid);
@@ -1047,7 +847,14 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // reads of the stages that the next iteration's DMA refills.  "Tile -1" is an
   // all-masked dummy (S = -inf, P = 0, its V stage DMA'd from an empty tile: zeros),
   // and the sequence ends with one empty tile whose iteration finishes the last one.
-  static_assert(2 * KK == 16 && 4 * DT == 16 && DMA_PER_WAVE == 4, "the MFMA runs are laid out for d = 128");
+  // At d = 64 a run is 16 MFMAs, each carrying a slot of both streams: the softmax VALU
+  // work, which does not depend on d, then bounds the tile.
+  constexpr int NRUN = 4 * KK;                          // MFMAs per run (both halves)
+  constexpr bool BOTH = NRUN == 16;                     // a slot of both streams per MFMA
+  constexpr int FIRST = BOTH ? NRUN - 2 : NRUN / 2 - 1; // slots that ride on the PV run
+  constexpr int TAIL = FIRST + (BOTH ? NRUN : NRUN / 2);
+  static_assert(4 * DT == NRUN / 2 && 2 * KK == NRUN / 2, "QK and PV runs of one length");
+  constexpr int DMA_EVERY = NRUN / DMA_PER_WAVE, DMA_AT = DMA_EVERY == 8 ? 5 : DMA_EVERY / 2;
   f32x16 sa0[2], sa1[2], sb0[2], sb1[2];
   bf16x8 pb0[4], pb1[4];
   // the first tile's max of a half's S in scaled log2 units, from both lanes of each
@@ -1077,15 +884,23 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
     pb0[j] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
     pb1[j] = pb0[j];
   }
-  tq0[14] = tq1[14] = -INFINITY;  // the dummy tile's streams enter the loop at slot 15
-  uq0[12] = uq0[13] = uq1[12] = uq1[13] = 0.f;
-  int prev_nvalid = 0;
+  tq0[FIRST - 1] = tq1[FIRST - 1] = -INFINITY;  // the dummy tile's streams enter the loop at slot FIRST
+  uq0[FIRST - 3] = uq0[FIRST - 2] = uq1[FIRST - 3] = uq1[FIRST - 2] = 0.f;
+  const int2 empty = make_int2(0, 0);
+  int2 prev = empty;
 
   int2 cur = scalar_tile(next_tile_raw());
-  int2 t1 = scalar_tile(next_tile_raw());
-  issue(make_int2(0, 0), kStages - 1);  // V of tile -1
-  issue(cur, 0);
-  issue(t1, 1);
+  bool cur_more = more, t1_more = false;  // whether any stream has a tile t, t + 1
+  int2 t1 = empty;
+  if constexpr (kDeep) {
+    t1 = scalar_tile(next_tile_raw());
+    t1_more = more;
+    issue(empty, kStages - 1, empty, kStages - 1);  // V of tile -1
+    issue(cur, 0, cur, 0);
+    issue(t1, 1, t1, 1);
+  } else {
+    issue(cur, 0, empty, 1);  // K of tile 0, V of tile -1
+  }
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
     q0[kk] = __builtin_bit_cast(bf16x8, qx0[kk]);
@@ -1098,16 +913,18 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // the loop, where any wait it inserted would also drain the DMA in flight, which it
   // does not see); of the DMA, the dummy stage and tile 0 must land before the loop,
   // tile 1 may still be in flight.
-  __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * DMA_PER_WAVE));
+  constexpr int IN_FLIGHT = kDeep ? 2 * DMA_PER_WAVE : 0;
+  __builtin_amdgcn_s_waitcnt(vmcnt_only(IN_FLIGHT));
   lds_barrier();
 
-  // Iteration t (t mod 4 = T, a compile-time constant, as are the stages) with tile
+  // Iteration t (t mod kStages = T, a compile-time constant, as are the stages) with tile
   // t-1's S in (so0, so1) and tile t's formed in (sn0, sn1); consecutive iterations
   // swap the two, so that no S is ever copied.  Returns false after the iteration of
   // the empty tile that ends the sequence.
   auto iteration = [&](f32x16 (&so0)[2], f32x16 (&so1)[2], f32x16 (&sn0)[2], f32x16 (&sn1)[2], auto tmod) {
     constexpr int T = decltype(tmod)::value;
-    constexpr int kst = T, vst = (T + kStages - 1) % kStages, st2 = (T + 2) % kStages;
+    constexpr int kst = T, vst = (T + kStages - 1) % kStages;
+    constexpr int k_into = kDeep ? (T + 2) % kStages : vst, v_into = kDeep ? k_into : T;
     bf16x8 kf[2 * KK], vf[4 * DT];
     if (wave_live) {
       kf[0] = k_frag(kst, 0);
@@ -1116,25 +933,26 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       kf[3] = k_frag(kst, 3);
     }
     const int2 t2 = scalar_tile(next_tile_raw());  // every thread; refills the table at its end
+    const int2 v_tile = kDeep ? t2 : cur;          // the tiles whose K and V arrive during this iteration: t2 and this
     const int cur_nvalid = cur.y & 255;
     if (wave_live) {
       // ---- QK run
 #pragma unroll
-      for (int i = 0; i < 32; ++i) {
+      for (int i = 0; i < NRUN; ++i) {
         const int f = i / 2;
         if (i % 2 == 0) {
           sn0[f / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f], q0[f % KK], f % KK ? sn0[f / KK] : f32x16{}, 0, 0, 0);
-          soft_slot(so0, ms0, acc0, pb0, tq0, uq0, 15 + f);
-          if (f + 4 < 2 * KK) kf[f + 4] = k_frag(kst, f + 4);
         } else {
           sn1[f / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f], q1[f % KK], f % KK ? sn1[f / KK] : f32x16{}, 0, 0, 0);
-          soft_slot(so1, ms1, acc1, pb1, tq1, uq1, 15 + f);
         }
-        if (i % 8 == 5) issue_part(t2, st2, i / 8);
+        if (BOTH || i % 2 == 0) soft_slot(so0, ms0, acc0, pb0, tq0, uq0, FIRST + (BOTH ? i : f));
+        if (BOTH || i % 2 == 1) soft_slot(so1, ms1, acc1, pb1, tq1, uq1, FIRST + (BOTH ? i : f));
+        if (i % 2 == 0 && f + 4 < 2 * KK) kf[f + 4] = k_frag(kst, f + 4);
+        if (i % DMA_EVERY == DMA_AT) issue_part(t2, k_into, v_tile, v_into, i / DMA_EVERY);
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int g = 31; g < 34; ++g) {
+      for (int g = TAIL; g < 34; ++g) {
         soft_slot(so0, ms0, acc0, pb0, tq0, uq0, g);
         soft_slot(so1, ms1, acc1, pb1, tq1, uq1, g);
       }
@@ -1143,8 +961,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       vf[0] = v_frag(vst, 0);
       vf[1] = v_frag(vst, 1);
       vf[2] = v_frag(vst, 2);
-      settle(ms0, l0, acc0, o0, pb0, q0, vst, prev_nvalid);
-      settle(ms1, l1, acc1, o1, pb1, q1, vst, prev_nvalid);
+      settle(ms0, l0, acc0, o0, pb0, q0, vst, prev);
+      settle(ms1, l1, acc1, o1, pb1, q1, vst, prev);
       acc0 = 0.f;
       acc1 = 0.f;
       if (__builtin_expect(cur_nvalid < kTileKeys, 0)) {
@@ -1156,15 +974,15 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         ms0 = tile_max(sn0);
         ms1 = tile_max(sn1);
       }
-      // ---- PV run.  Stream slot (g, half) of tile t rides on MFMA 2 g + half + 2,
-      // past the last MFMA that reads the previous tile's P fragment it overwrites.
+      // ---- PV run.  Stream slot (g, half) of tile t rides on MFMA 2 g + half + 2 (g + 2 at
+      // d = 64), past the last MFMA that reads the previous tile's P fragment it overwrites.
       // An MFMA reads its A and B registers over its passes, so each MFMA's operands
       // are held (an empty asm use) until the end of the next slot, when it has
       // finished: the compiler, which does not see these MFMAs, would otherwise give
       // the registers to the next value as soon as the MFMA is issued.
       bf16x8 hold_a = vf[0], hold_b = pb0[0];
 #pragma unroll
-      for (int i = 0; i < 32; ++i) {
+      for (int i = 0; i < NRUN; ++i) {
         const int f = i / 2;
         const bf16x8 op_a = vf[f], op_b = i % 2 ? pb1[f / DT] : pb0[f / DT];
         if (i % 2 == 0) {
@@ -1174,8 +992,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
           pv_mfma(o1[f % DT], op_a, op_b);
         }
         if (i >= 2) {
-          if (i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, (i - 2) / 2);
-          else soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, (i - 2) / 2);
+          if (BOTH || i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, BOTH ? i - 2 : f - 1);
+          if (BOTH || i % 2 == 1) soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, BOTH ? i - 2 : f - 1);
         }
         if (i > 0) asm volatile("" ::"v"(hold_a), "v"(hold_b));
         hold_a = op_a;
@@ -1184,22 +1002,27 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       }
       asm volatile("s_nop 7\n\ts_nop 3" ::"v"(hold_a), "v"(hold_b));  // the last MFMA's operands
     } else {
-      issue(t2, st2);
+      issue(t2, k_into, v_tile, v_into);
     }
-    // ---- tile t+1 has landed (the DMA of tile t+2 may still be in flight) and every
-    // wave is past its reads of the stages refilled next
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * DMA_PER_WAVE));
+    // ---- what iteration t+1 reads has landed (with four stages the DMA of tile t+2 may
+    // still be in flight) and every wave is past its reads of the stages refilled next
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(IN_FLIGHT));
     lds_barrier();
-    cur = t1;
+    prev = cur;
+    const bool go_on = KS == 1 ? cur_nvalid != 0 : cur_more;
+    cur = kDeep ? t1 : t2;
+    cur_more = kDeep ? t1_more : more;
     t1 = t2;
-    prev_nvalid = cur_nvalid;
-    return cur_nvalid != 0;
+    t1_more = more;
+    return go_on;
   };
   for (;;) {
     if (!iteration(sa0, sa1, sb0, sb1, std::integral_constant<int, 0>{})) break;
     if (!iteration(sb0, sb1, sa0, sa1, std::integral_constant<int, 1>{})) break;
-    if (!iteration(sa0, sa1, sb0, sb1, std::integral_constant<int, 2>{})) break;
-    if (!iteration(sb0, sb1, sa0, sa1, std::integral_constant<int, 3>{})) break;
+    if constexpr (kStages == 4) {
+      if (!iteration(sa0, sa1, sb0, sb1, std::integral_constant<int, 2>{})) break;
+      if (!iteration(sb0, sb1, sa0, sa1, std::integral_constant<int, 3>{})) break;
+    }
   }
   __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // no DMA may land in the stages reused below
   __syncthreads();
@@ -1208,43 +1031,132 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // permuted like K), store rows with 16-byte nontemporal writes (each row is written
   // once, and the L2 then holds no dirty lines of O for the end of the kernel to
   // write back)
-  uint8_t* const stage_o = k_ring + wave * kR64TileBytes;  // 64 rows x 256 B per wave
-  auto finish = [&](f32x16 (&o)[DT], float ms, float l, int g) {
-    const float l_tot = pair_sum(l);
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    const int r = 32 * g + lane % 32;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        bf16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(o[dt][4 * i4 + e] * inv);
-        // d = 32 dt + 8 i4 + 4 half: chunk 4 dt + i4, byte 8 half within it
-        *reinterpret_cast<bf16x4*>(stage_o + k_pos(r, 4 * dt + i4) + 8 * half) = w;
-      }
-    const int qr = wrow + r;
-    if (a.lse && lane < 32 && qr < row_end)
-      a.lse[static_cast<int64_t>(h) * a.lq + qr] = l_tot > 0.f ? (ms + __log2f(l_tot)) * kLn2 : -INFINITY;
-  };
-  if (wave_live) {
-    acc_settled(o0);
-    acc_settled(o1);
-    finish(o0, ms0, l0, 0);
-    finish(o1, ms1, l1, 1);
-  }
-  __syncthreads();
+  constexpr int STAGE = 64 * L::ROW;  // 64 rows per wave
   uint16_t* op = static_cast<uint16_t*>(a.out);
-  if (wave_live) {
+  auto store_rows = [&](const uint8_t* stage_o) {  // the wave's share of its rows' chunks
 #pragma unroll
-    for (int i = 0; i < 64 * 16 / kWave; ++i) {
-      const int cid = lane + i * kWave;
-      const int r = cid / 16, ch = cid % 16;
+    for (int i = 0; i < 64 * L::CHUNKS / kWave / KS; ++i) {
+      const int cid = stream * kWave + lane + i * KS * kWave;
+      const int r = cid / L::CHUNKS, ch = cid % L::CHUNKS;
       const int qrow = wrow + r;
       if (qrow < row_end)
-        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage_o + k_pos(r, ch)),
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage_o + L::k_pos(r, ch)),
                                     reinterpret_cast<u32x4*>(op + (static_cast<int64_t>(qrow) * a.H + h) * D + ch * 8));
     }
+  };
+  if constexpr (KS == 1) {
+    uint8_t* const stage_o = k_ring + wave * STAGE;
+    auto finish = [&](f32x16 (&o)[DT], float ms, float l, int g) {
+      const float l_tot = pair_sum(l);
+      const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+      const int r = 32 * g + lane % 32;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          bf16x4 w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(o[dt][4 * i4 + e] * inv);
+          // d = 32 dt + 8 i4 + 4 half: chunk 4 dt + i4, byte 8 half within it
+          *reinterpret_cast<bf16x4*>(stage_o + L::k_pos(r, 4 * dt + i4) + 8 * half) = w;
+        }
+      const int qr = wrow + r;
+      if (a.lse && lane < 32 && qr < row_end)
+        a.lse[static_cast<int64_t>(h) * a.lq + qr] = l_tot > 0.f ? (ms + __log2f(l_tot)) * kLn2 : -INFINITY;
+    };
+    if (wave_live) {
+      acc_settled(o0);
+      acc_settled(o1);
+      finish(o0, ms0, l0, 0);
+      finish(o1, ms1, l1, 1);
+    }
+    __syncthreads();
+    if (wave_live) store_rows(stage_o);
+  } else {
+    // The streams' partial results of a row wave's 64 rows meet in LDS.  A unit is 32 rows
+    // (half g) x 32 of d (dt), 16 values a lane; every unit has an owner among the
+    // streams, the others hand it theirs, scaled to the rows' common max.
+    constexpr int UNITS = KS == 2 ? DT : 2 * DT;  // slots for units handed over, per wave (4 KB each)
+    static_assert(KS == 2 || DT == 2, "one unit per stream");
+    static_assert(kR64Waves * UNITS * 4096 <= kRing && RW * STAGE <= kRing, "the rings hold the exchange and the output");
+    auto owner = [](int g, int dt) { return KS == 2 ? g : g + 2 * dt; };
+    float* const m_of = reinterpret_cast<float*>(table);  // [wave][64 rows]
+    float* const l_of = m_of + kR64Waves * 64;
+    static_assert(2 * kR64Waves * 64 * sizeof(float) <= sizeof(table), "the table holds the rows' max and sum");
+    const float lt0 = pair_sum(l0), lt1 = pair_sum(l1);
+    m_of[wave * 64 + lane] = half ? ms1 : ms0;
+    l_of[wave * 64 + lane] = half ? lt1 : lt0;
+    __syncthreads();
+    float mt[2], lt[2], wt[2];  // per half: the row's max and sum over the streams, this stream's weight
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+      float m[KS];
+      mt[g] = kNoMax;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        m[j] = m_of[(j * RW + wave_r) * 64 + 32 * g + lane % 32];
+        mt[g] = fmaxf(mt[g], m[j]);
+      }
+      lt[g] = 0.f;
+#pragma unroll
+      for (int j = 0; j < KS; ++j)
+        lt[g] = fmaf(__builtin_amdgcn_exp2f(m[j] - mt[g]), l_of[(j * RW + wave_r) * 64 + 32 * g + lane % 32], lt[g]);
+      wt[g] = __builtin_amdgcn_exp2f((g ? ms1 : ms0) - mt[g]);
+    }
+    auto unit = [&](int w, int g, int dt) {  // where wave w puts unit (g, dt)
+      return reinterpret_cast<f32x4*>(k_ring) + ((w * UNITS + (KS == 2 ? dt : 2 * g + dt)) * 4) * kWave + lane;
+    };
+    if (wave_live) {
+      acc_settled(o0);
+      acc_settled(o1);
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          if (stream != owner(g, dt)) {  // wave-uniform
+            f32x4* const to = unit(wave, g, dt);
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+              f32x4 x;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = (g ? o1 : o0)[dt][4 * i4 + e] * wt[g];
+              to[i4 * kWave] = x;
+            }
+          }
+    }
+    __syncthreads();
+    uint8_t* const stage_o = v_ring + wave_r * STAGE;
+    if (wave_live) {
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const float inv = lt[g] > 0.f ? 1.0f / lt[g] : 0.f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+          if (stream == owner(g, dt)) {
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+              f32x4 x;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = (g ? o1 : o0)[dt][4 * i4 + e] * wt[g];
+#pragma unroll
+              for (int j = 1; j < KS; ++j) {  // the other streams' in one order, from the next on
+                const f32x4 y = unit(((stream + j) % KS) * RW + wave_r, g, dt)[i4 * kWave];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] += y[e];
+              }
+              bf16x4 w;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(x[e] * inv);
+              *reinterpret_cast<bf16x4*>(stage_o + L::k_pos(32 * g + lane % 32, 4 * dt + i4) + 8 * half) = w;
+            }
+            const int qr = wrow + 32 * g + lane % 32;
+            if (dt == 0 && a.lse && lane < 32 && qr < row_end)
+              a.lse[static_cast<int64_t>(h) * a.lq + qr] = lt[g] > 0.f ? (mt[g] + __log2f(lt[g])) * kLn2 : -INFINITY;
+          }
+      }
+    }
+    __syncthreads();
+    if (wave_live) store_rows(stage_o);
   }
 }
 
@@ -1475,29 +1387,73 @@ __global__ __launch_bounds__(F32Shape<D>::NW* kWave, 2) void k_attn_f32(AttnArgs
   }
 }
 
+constexpr int kMaxDevices = 64;
+
+// The current device, or -1 where its cached values have no slot.
+int current_device() {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices ? dev : -1;
+}
+
+// The current device's CUs, looked up once per device.
+int device_cus() {
+  static std::atomic<int> known[kMaxDevices];
+  const int dev = current_device();
+  int n = dev >= 0 ? known[dev].load(std::memory_order_relaxed) : 0;
+  if (n <= 0) {
+    if (dev < 0 || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+      n = 256;
+    if (dev >= 0) known[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
 // Workgroups of the one-wave-per-group kernel: one wave per group, at most as many
 // workgroups as the device holds at once (its CU count times the kernel's
 // occupancy, looked up once per device).
 template <int D>
 int group_workgroups(int64_t groups) {
-  constexpr int kMaxDevices = 64;
   static std::atomic<int> resident[kMaxDevices];
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) dev = -1;
+  const int dev = current_device();
   int n = dev >= 0 ? resident[dev].load(std::memory_order_relaxed) : 0;
   if (n <= 0) {
-    int cus = 0, per_cu = 0;
-    if (dev < 0 || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-      cus = 256;
+    int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_bf16_groups<D>, kGrpWaves * kWave, 0) !=
             hipSuccess ||
         per_cu <= 0)
       per_cu = 1;
-    n = cus * per_cu;
+    n = device_cus() * per_cu;
     if (dev >= 0) resident[dev].store(n, std::memory_order_relaxed);
   }
   const int64_t need = (groups + kGrpWaves - 1) / kGrpWaves;
   return static_cast<int>(need < n ? need : n);
+}
+
+// Key streams of the 64-row kernel (1, 2, or with d = 64 up to 4) for `groups` (head, group)
+// pairs of `rows` rows: a workgroup of KS streams takes 256 / KS rows and 1 / KS of the
+// time, and the CUs run one workgroup at a time, so the time goes as the rounds of
+// workgroups over CUs times (1 / KS + what a workgroup's start and end take, about 5 of
+// the 64 tiles of a usual list).Measured on 256 CUs with
+// one stream (d = 64: the earlier 32-row kernel) and with the streams chosen here:
+// 5 heads x 3 groups x 1,560 rows, 32 blocks of 128, d = 128: 105 workgroups, 104.7 us;
+//   two streams, 195 workgroups, 62.4-64 us;
+// 16 heads x 1,560 rows over 75 blocks of 64, d = 64: 112 workgroups, 108 us; two streams,
+//   208 workgroups, 54.9 us.
+// 12 heads x 4,680 rows (228 workgroups, or 444 in two rounds) stays with one.
+template <int D>
+int key_streams(int64_t groups, int rows, int cus) {
+  int best = 1;
+  double least = 0;
+  for (int ks = 1; ks <= (D == 128 ? 2 : 4); ks *= 2) {
+    const int per_wg = kR64Waves * 64 / ks;
+    const int64_t rounds = (groups * ((rows + per_wg - 1) / per_wg) + cus - 1) / cus;
+    const double time = rounds * (1.0 / ks + 0.08);
+    if (ks == 1 || time < least) {
+      best = ks;
+      least = time;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -1527,27 +1483,35 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
   a.out = L.out;
   a.lse = L.lse;
   const int rows = L.group_size < L.lq ? L.group_size : L.lq;
-  // bf16, d = 128 and groups of more than 32 rows: 64 rows per wave; else 32
-  const bool r64 = g.dtype == 0 && g.D == 128 && rows > 32;
-  const bool small = rows <= 32;  // one 32-row tile per group: a wave per group
-  const int rows_per_wg = g.dtype != 0 ? kF32Rows : r64 ? kR64Waves * 64 : small ? 32 : kWaves * 32;
-  a.tiles_per_group = (rows + rows_per_wg - 1) / rows_per_wg;
-  const int64_t nwg = static_cast<int64_t>(g.H) * L.R * a.tiles_per_group;
-  if (nwg <= 0) return hipSuccess;
-  if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
-  const dim3 grid(static_cast<unsigned>(nwg));
-  // bf16 with d = 128 and more than 32 rows per group always takes the 64-row kernel
-  if (r64) return launch_kernel(k_attn_bf16_r64<128>, grid, dim3(kR64Waves * kWave), 0, stream, a);
-  if (g.dtype == 0) {
-    if (!small) return launch_kernel(k_attn_bf16<64, kWaves>, grid, dim3(kWaves * kWave), 0, stream, a);
-    if (g.D == 128)
-      return launch_kernel(k_attn_bf16_groups<128>, dim3(group_workgroups<128>(nwg)), dim3(kGrpWaves * kWave), 0,
-                           stream, a);
-    return launch_kernel(k_attn_bf16_groups<64>, dim3(group_workgroups<64>(nwg)), dim3(kGrpWaves * kWave), 0, stream,
-                         a);
+  const int64_t groups = static_cast<int64_t>(g.H) * L.R;
+  if (groups <= 0 || groups > 0x7fffffff) return groups <= 0 ? hipSuccess : hipErrorInvalidConfiguration;
+  auto launch = [&](auto kernel, int rows_per_wg, int threads) {
+    a.tiles_per_group = (rows + rows_per_wg - 1) / rows_per_wg;
+    const int64_t nwg = groups * a.tiles_per_group;
+    if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
+    return launch_kernel(kernel, dim3(static_cast<unsigned>(nwg)), dim3(threads), 0, stream, a);
+  };
+  if (g.dtype != 0) {
+    if (g.D == 128) return launch(k_attn_f32<128>, kF32Rows, F32Shape<128>::NW * kWave);
+    return launch(k_attn_f32<64>, kF32Rows, F32Shape<64>::NW * kWave);
   }
-  if (g.D == 128) return launch_kernel(k_attn_f32<128>, grid, dim3(F32Shape<128>::NW * kWave), 0, stream, a);
-  return launch_kernel(k_attn_f32<64>, grid, dim3(F32Shape<64>::NW * kWave), 0, stream, a);
+  if (rows <= 32) {  // one 32-row tile per group: a wave per group
+    a.tiles_per_group = 1;
+    const dim3 threads(kGrpWaves * kWave);
+    if (g.D == 128)
+      return launch_kernel(k_attn_bf16_groups<128>, dim3(group_workgroups<128>(groups)), threads, 0, stream, a);
+    return launch_kernel(k_attn_bf16_groups<64>, dim3(group_workgroups<64>(groups)), threads, 0, stream, a);
+  }
+  constexpr int kThreads = kR64Waves * kWave, kRows = kR64Waves * 64;
+  if (g.D == 128) {
+    if (key_streams<128>(groups, rows, device_cus()) == 2) return launch(k_attn_bf16_r64<128, 2>, kRows / 2, kThreads);
+    return launch(k_attn_bf16_r64<128, 1>, kRows, kThreads);
+  }
+  switch (key_streams<64>(groups, rows, device_cus())) {
+    case 4: return launch(k_attn_bf16_r64<64, 4>, kRows / 4, kThreads);
+    case 2: return launch(k_attn_bf16_r64<64, 2>, kRows / 2, kThreads);
+    default: return launch(k_attn_bf16_r64<64, 1>, kRows, kThreads);
+  }
 }
 
 }  // namespace omnimem

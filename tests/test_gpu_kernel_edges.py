@@ -86,3 +86,49 @@ def test_fp32_attention_long(dev, d, n):
     say(f"  max-abs {err:.2e}")
     assert err <= 1e-4
     assert np.allclose(lse.cpu().numpy()[hs, qs], l_ref, rtol=2e-6, atol=1e-5)
+
+
+# The 64-row bf16 kernel in each of its key-stream counts (chosen by how many workgroups
+# the grid has): block lists of every length, in any order, with tail blocks of 8 tokens,
+# padding, duplicates, non-resident blocks, scores that jump between blocks far above
+# the running max, lists of more than one decoded stretch (256 entries) and of an odd
+# number of tiles.
+@pytest.mark.parametrize("d,H,Lq,G,K,streams", [(128, 2, 300, 130, 25, 2), (128, 2, 33, 33, 601, 2),
+                                                (128, 2, 32000, 250, 25, 1), (128, 2, 32000, 250, 601, 1),
+                                                (64, 2, 300, 130, 25, 4), (64, 3, 65, 65, 601, 4),
+                                                (64, 8, 2100, 2100, 25, 2), (64, 8, 2100, 2100, 601, 2),
+                                                (64, 2, 32000, 250, 25, 1), (64, 2, 32000, 250, 601, 1)])
+def test_key_streams(dev, d, H, Lq, G, K, streams):
+    say(f"key streams d={d} H={H} Lq={Lq} G={G} K={K}: {streams}")
+    S, B, n = 200, 64, 5
+    nb = n * 4
+    g = torch.Generator().manual_seed(d + K)
+    u = torch.randn(H, d, generator=g)
+    u = 3.0 * u / u.norm(dim=-1, keepdim=True)
+    q = (u + 0.3 * torch.randn(Lq, H, d, generator=g)).to(torch.bfloat16)
+    jump = torch.tensor([1.0, 40.0, 1.0, 0.5, 400.0, 2.0, 0.25, 60.0, 1.0, 3.0, 400.0, 1.0, 0.1, 8.0, 1.0, 50.0, 1.0, 0.3,
+                         20.0, 1.0])
+    tokens = torch.arange(S) // B
+    k = (u + 0.3 * torch.randn(n, S, H, d, generator=g)) * jump.view(n, 4)[:, tokens].view(n, S, 1, 1)
+    k = k.to(torch.bfloat16)
+    v = torch.randn(n, S, H, d, generator=g).to(torch.bfloat16)
+    cache = synth.page_layer(k.to(dev), v.to(dev), B, seed=K, pad_value=NAN, nonresident=[2, 9])
+    resident = synth.resident_mask(cache).numpy()
+    R = -(-Lq // G)
+    idx, cnt = random_lists(np.random.default_rng(K + d), H, R, K, nb)
+    if R > 1:
+        cnt[:, 1] = 1
+        idx[:, 1, 0] = 3   # nothing but a tail block
+    qd, scale = q.to(dev), d ** -0.5
+    out, lse = omnimem_sparse_attn(cache, qd, torch.from_numpy(idx).to(dev), torch.from_numpy(cnt).to(dev), G, scale)
+    dout, dlse = omnimem_dense_attn(cache, qd, 0, n, scale)
+    rng = np.random.default_rng(7)
+    m = 400
+    hs, qs = rng.integers(0, H, m).astype(np.int32), rng.integers(0, Lq, m).astype(np.int32)
+    qs[:50] = rng.integers(0, min(2 * G, Lq), 50)
+    qs[50:70] = Lq - 1 - rng.integers(0, min(G, 70), 20)
+    oi = np.where(idx >= nb, -1, idx).astype(np.int32)
+    ref = oracle.sparse_attn(q, k, v, B, oi, cnt, G, scale, resident=resident, hs=hs, qs=qs)
+    check((out, lse), ref, torch.bfloat16, "sparse")
+    ref = oracle.dense_attn(q, k, v, B, 0, n, scale, resident=resident, hs=hs, qs=qs)
+    check((dout, dlse), ref, torch.bfloat16, "dense")
