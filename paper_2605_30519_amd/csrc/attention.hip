@@ -34,7 +34,6 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kTileKeys = 64;  // keys per attention tile (one B = 64 block, half of a B = 128 block)
 
 struct AttnArgs {
   const void* q;
@@ -465,60 +464,6 @@ __device__ __forceinline__ void keep_here(const bf16x8 (&pb)[4], float l) {
   asm volatile("" ::"v"(pb[0]), "v"(pb[1]), "v"(pb[2]), "v"(pb[3]), "v"(l));
 }
 
-// Workgroup barrier for LDS traffic only.  __syncthreads() also orders global memory,
-// which makes every wave drain its outstanding loads, including the DMA of tiles
-// meant to stay in flight across the barrier; LDS written by DMA is covered by the
-// explicit vmcnt wait before it, and the asm statements keep the compiler from
-// moving LDS accesses across it.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// LDS tiles of the 64-row kernel: 64 rows of 2 d bytes, unpadded, with the 16-byte
-// chunks of each row permuted so that both the K fragment reads (one chunk of 16 rows a
-// pass) and the transposing V reads (4 chunks of 4 rows a pass) touch every bank once:
-//   K: chunk c of row r sits at chunk position c ^ (r mod 16), for d = 64, where two rows
-//      span the banks, at c ^ (r / 2 mod 8)
-//   V: at c ^ 4 (r mod 4), for d = 64 at c ^ 4 (r / 2 mod 2)
-// Tiles arrive by buffer-to-LDS DMA: one instruction moves 64 lanes x 16 bytes into a
-// contiguous 1 KB (4 rows, for d = 64 8), lane l filling position l mod (d / 8) of its
-// row, so each lane fetches the global chunk that belongs at its position.
-template <int D>
-struct R64Lds {
-  static constexpr int ROW = D * 2;                 // bytes per row
-  static constexpr int TILE = kTileKeys * ROW;      // bytes per tile, K or V
-  static constexpr int CHUNKS = D / 8;              // 16-byte chunks per row
-  static constexpr int DMA_ROWS = 1024 / ROW;       // rows per DMA instruction
-  __device__ __forceinline__ static int k_pos(int r, int c) {
-    return r * ROW + ((c ^ (D == 128 ? r & 15 : (r >> 1) & 7)) << 4);
-  }
-  __device__ __forceinline__ static int v_pos(int r, int c) {
-    return r * ROW + ((c ^ (D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1))) << 4);
-  }
-};
-
-// s_waitcnt operand that waits for at most n outstanding vector-memory operations
-// and for nothing else (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
-constexpr int vmcnt_only(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
-
-// Buffer resource (raw, stride 0) over `bytes` bytes at p, in scalar registers; the
-// caller guarantees p and bytes are the same in every lane.  Offsets at or past the
-// end read as zero.
-__device__ __forceinline__ u32x4 buffer_rsrc(const void* p, int bytes) {
-  const uint64_t u = reinterpret_cast<uint64_t>(p);
-  u32x4 r;
-  r[0] = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u));
-  r[1] = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32) & 0xffffu);
-  r[2] = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(bytes));
-  r[3] = 0x00020000u;
-  return r;
-}
-
-__device__ __forceinline__ uint32_t lds_offset(const void* p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));
-}
 // P V product with its accumulator in AccVGPRs.  Selected by the compiler, every
 // MFMA accumulator sits in the VGPRs that the softmax VALU work also uses, and an
 // MFMA writing its result there slows that work down; the asm keeps O in AccVGPRs.
@@ -542,23 +487,12 @@ __device__ __forceinline__ void acc_settled(f32x16 (&o)[2]) {
 }
 
 
-// One buffer-to-LDS DMA instruction: lane l's 16 bytes at rsrc + voffset land at LDS
-// byte lds + 16 l.  It is written as inline asm so that the compiler does not track
-// it as an LDS store (it would make every later LDS read wait for all DMA in flight);
-// the kernel orders it itself, with explicit vmcnt waits before the barriers that
-// publish a stage.
-__device__ __forceinline__ void dma_16x64(u32x4 rsrc, int voffset, uint32_t lds) {
-  // M0 (the LDS destination) is set by the compiler; the s_nop is the wait state an
-  // LDS DMA needs after an M0 write
-  asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(voffset), "s"(rsrc), "{m0}"(lds) : "memory");
-}
-
 // KS key streams: the workgroup's waves are KS sets of 4 / KS row waves, set j walking
 // tiles j, j + KS, ... of the list and the sets meeting in LDS at the end, for grids that
 // would leave CUs idle with 256 rows per workgroup.
 template <int D, int KS>
 __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs a) {
-  using L = R64Lds<D>;
+  using L = KeyTileLds<D>;
   constexpr int NT = kR64Waves * kWave;
   constexpr int RW = kR64Waves / KS;  // row waves per stream
   constexpr int ROWS = RW * 64;

@@ -10,24 +10,35 @@
 // that keeps the residual, the pieces are its pooled-key pages and residual pages,
 // written once per chunk when the chunk is pooled; otherwise k_split_keys splits the
 // fp32 pooled keys once per call, tile by tile (64 keys, hi then lo).  Either way a
-// workgroup stages a tile with plain coalesced 16-byte loads.
+// tile goes to LDS as it stands.
 // k_prob_partial: one workgroup per (head, slice of at most 128 query rows), the
 // slices of one head contiguous on one XCD so that its L2 holds that head's keys.
 // Each wave owns 64 rows (two 32-row MFMA tiles that share every key fragment) and
-// 32 keys of each tile; a slice that is part of one group double-buffers the key
-// tiles in LDS (one barrier per tile), a slice of whole groups stages each tile
-// between two barriers, its LDS holding the probability tile that it reduces per
-// group.  The workgroup walks the tiles twice: first for each row's LSE
+// 32 keys of each tile.  The workgroup walks the tiles twice: first for each row's LSE
 // (online, exp2 domain, the hardware exp2: probabilities below 2^-126 count as 0),
-// then for exp(u - LSE) summed over the rows of each group segment of the slice.  The products are bf16 MFMA (32x32x16) with fp32
-// accumulation: hi*q + lo*q for bf16 queries (exact), plus hi*q_lo for fp32 queries
-// split the same way.  The first pass forms S^T = K Q^T (a lane owns one query
-// row: its max and sum stay in the lane), the second S = Q K^T (a lane owns one
-// key: the sum over a group's rows is a sum over the lane's accumulator rows).
+// then for exp(u - LSE) summed over the rows of each group segment of the slice.  The
+// products are bf16 MFMA (32x32x16) with fp32 accumulation: hi*q + lo*q for bf16 queries
+// (exact), plus hi*q_lo for fp32 queries split the same way.  The first pass forms
+// S^T = K Q^T (a lane owns one query row: its max and sum stay in the lane), the second
+// S = Q K^T (a lane owns one key: the sum over a group's rows is a sum over the lane's
+// accumulator rows).
+//
+// The MFMAs bound it (four times the contraction's flops: two passes, two pieces), so a
+// step is built to keep them fed: the next tile comes to LDS by DMA while this one is
+// used, one barrier a step, and each MFMA of tile t carries the exponential of one
+// score of tile t - 1 (for bf16 queries; fp32 ones have no registers left for two
+// tiles' scores).  One group of 4,680 rows, 12 heads, 1,480 keys, d = 128: 110 -> 80 us
+// for the kernel (1.06 PFLOP/s of MFMA work; 444 workgroups leave the fuller CUs 49 us
+// of MFMAs at the 2.0 GHz it runs at), against two barriers' worth of waiting a step with
+// tiles staged through registers.
+// A slice of whole groups reduces a 128 x 64 probability tile per group through LDS in
+// its second pass, where that tile takes the place of the second key buffer.
 // The group means become the order-preserving keys that k_topk ranks (0 outside
 // Omega): written by k_prob_partial when its slice holds whole groups, else by
 // k_prob_merge, which sums a group's slices in a fixed order.
 #include <math.h>
+
+#include <type_traits>
 
 #include "device_common.h"
 #include "launch.h"
@@ -39,8 +50,9 @@ constexpr int kPThreads = 256;
 constexpr int kPRows = kProbSliceRows;  // query rows per slice: 64 per wave, two waves deep
 static_assert(kPRows == 128, "the wave layout assumes 128-row slices");
 constexpr int kPKeys = 64;    // pooled keys per tile: 32 per wave, two waves wide
-static_assert(kPKeys == kCmpPageTokens, "a key tile is one page of the compressed cache");
+static_assert(kPKeys == kCmpPageTokens && kPKeys == kTileKeys, "a key tile is one page of the compressed cache");
 constexpr int kPRedStride = kPKeys + 1;
+constexpr float kPNoMax = -1.0e30f;  // running max before the first key: finite, below any score
 constexpr float kLog2eP = 1.4426950408889634f;
 
 template <typename T>
@@ -132,10 +144,8 @@ __global__ __launch_bounds__(kPThreads) void k_split_keys(const float* __restric
   }
 }
 
-// Split-key tiles: 16-byte chunk e of tile t (piece e / (64 CH), key row, chunk c)
-// is fetched by thread e mod 256 and goes to chunk c ^ (row mod CH) of its LDS
-// row, so that the fragment reads of 8 consecutive rows hit 8 different chunk
-// columns.
+// Split-key tiles through registers (the second pass over slices of whole groups): 16-byte
+// chunk e of tile t (piece e / (64 CH), key row, chunk c) is fetched by thread e mod 256.
 template <int D>
 __device__ __forceinline__ void fetch_tile(const ProbArgs& a, int h, int t, u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads]) {
   constexpr int PIECE_CHUNKS = kPKeys * D / 8;
@@ -149,41 +159,35 @@ __device__ __forceinline__ void fetch_tile(const ProbArgs& a, int h, int t, u32x
 }
 
 template <int D>
-__device__ __forceinline__ void stage_tile(const u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads], uint16_t* ktile) {
+__device__ __forceinline__ void stage_tile(const u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads], uint8_t* ktile) {
   constexpr int CH = D / 8;
 #pragma unroll
   for (int u = 0; u < 2 * kPKeys * CH / kPThreads; ++u) {
     const int e = threadIdx.x + u * kPThreads, piece = e / (kPKeys * CH), rem = e % (kPKeys * CH);
-    const int row = rem / CH, c = rem % CH;
-    *reinterpret_cast<u32x4*>(ktile + piece * kPKeys * D + row * D + 8 * (c ^ (row % CH))) = kv[u];
+    *reinterpret_cast<u32x4*>(ktile + piece * KeyTileLds<D>::TILE + KeyTileLds<D>::k_pos(rem / CH, rem % CH)) = kv[u];
   }
 }
 
-// The 8 bf16 of key row krow, d = 16 kk + 8 half + 0..7, of one piece (0 hi, 1 lo).
-template <int D>
-__device__ __forceinline__ bf16x8 key_frag(const uint16_t* ktile, int piece, int kk, int krow, int half) {
-  constexpr int CH = D / 8;
-  const int pc = (2 * kk + half) ^ (krow % CH);
-  return *reinterpret_cast<const bf16x8*>(ktile + piece * kPKeys * D + krow * D + 8 * pc);
-}
-
 // MULTI: the slice holds whole groups, and a 128 x 64 probability tile is reduced
-// through LDS; the key tile then has one LDS buffer, staged between two barriers.
-// Otherwise the slice is part of one group: two key-tile buffers, tile t + 1
-// staged right after tile t's MFMAs, one barrier per tile.
+// through LDS in the second pass.
 template <typename T, int D, bool MULTI>
 __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
+  using L = KeyTileLds<D>;
   constexpr int KK = D / 16;                      // MFMA steps over d
   constexpr int CH = D / 8;                       // 16-byte chunks per key row
   constexpr int LPT = 2 * kPKeys * CH / kPThreads;  // 16-byte loads per thread per tile
   constexpr int QP = QueryPieces<T>::N;
-  constexpr int NBUF = MULTI ? 1 : 2;
-  constexpr int TILE = 2 * kPKeys * D;            // bf16 elements of one split tile
-  __shared__ __align__(16) uint16_t ktile[NBUF * TILE];
-  // MULTI: the probability tile; else two buffers of the two row halves' key sums
-  __shared__ float red[MULTI ? kPRows * kPRedStride : 2 * 2 * kPKeys];
+  constexpr bool PIPE = QP == 1;                  // a tile's exponentials ride on the next tile's MFMAs
+  constexpr int TILE = 2 * L::TILE;               // bytes of one split tile: hi, then lo
+  constexpr int DMA = TILE / 1024 / (kPThreads / kWave);  // DMA instructions per wave and tile
+  constexpr int RED = MULTI ? kPRows * kPRedStride * 4 : 2 * 2 * kPKeys * 4;
+  // two key tiles; MULTI: the second one's place holds the probability tile in the second
+  // pass; else two buffers of the two row halves' key sums follow
+  constexpr int SECOND = MULTI && RED > TILE ? RED : TILE;
+  __shared__ __align__(1024) uint8_t lds[TILE + SECOND + (MULTI ? 0 : RED)];
   __shared__ float mrg_m[2][kPRows], mrg_l[2][kPRows];
   __shared__ float lse2[kPRows];
+  float* const red = reinterpret_cast<float*>(lds + TILE + (MULTI ? 0 : SECOND));
 
   const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int h = id / a.slices, slice = id % a.slices;
@@ -200,9 +204,36 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   }
   if (rows <= 0) return;  // workgroup-uniform, before any barrier
 
-  const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave, half = lane / 32;
+  const int tid = threadIdx.x, lane = tid % kWave, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int rh = wave & 1, kq = wave >> 1;  // rows [64 rh, +64) of the slice, keys [32 kq, +32) of a tile
   const int krow = 32 * kq + lane % 32;     // tile-local key this lane supplies
+
+  // ---- key tiles by DMA: instruction wave + 4 i of the tile's, piece i / (DMA / 2)
+  int src[DMA / 2];
+#pragma unroll
+  for (int i = 0; i < DMA / 2; ++i)
+    src[i] = L::k_pos(L::DMA_ROWS * (wave + 4 * i) + lane / L::CHUNKS, lane % L::CHUNKS);
+  const uint32_t dst0 = lds_offset(lds) + wave * 1024;
+  auto issue_part = [&](int t, int i) {  // instruction i of tile t, into buffer t mod 2
+    const int piece = i / (DMA / 2);
+    const int64_t off = t * a.tile_stride + h * a.head_stride;
+    dma_16x64(buffer_rsrc(a.piece[piece] + off, L::TILE), src[i % (DMA / 2)], dst0 + (t & 1) * TILE + 4 * i * 1024);
+  };
+  auto issue = [&](int t) {
+#pragma unroll
+    for (int i = 0; i < DMA; ++i) issue_part(t, i);
+  };
+  // this wave's LDS writes and DMA have landed, and every wave's
+  auto step_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x70);  // vmcnt 0, lgkmcnt 0
+    lds_barrier();
+  };
+  // fragment f = 2 kk + piece of buffer b: the 8 bf16 of key krow, d = 16 kk + 8 half + 0..7
+  auto key_frag = [&](int b, int f) {
+    return *reinterpret_cast<const bf16x8*>(lds + b * TILE + (f % 2) * L::TILE + L::k_pos(krow, 2 * (f / 2) + half));
+  };
+  issue(0);
 
   // query operands of the wave's two 32-row tiles: row 64 rh + 32 s + lane%32,
   // d = 16 kk + 8 half + 0..7 (zero past the slice)
@@ -230,65 +261,119 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
     }
   }
 
-  u32x4 kv[LPT];
   const float c2 = a.scale * kLog2eP;
+  const f32x16 none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY,
+                       -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  // One step's MFMAs, S of tile t from buffer t mod 2 into s[2], with tile t + 1 on its way;
+  // K_FIRST: S^T = K Q^T, else S = Q K^T.  ride(i) is called after MFMA i of 4 KK (i < 32
+  // at d = 128; at d = 64 it is called for 2 i and 2 i + 1).
+  auto products = [&](auto k_first, int t, f32x16 (&s)[2], auto ride) {
+    constexpr bool K_FIRST = decltype(k_first)::value;
+    constexpr int NF = 2 * KK, PER = 32 / (2 * NF), EVERY = 2 * NF / DMA;
+    auto mfma = [](const bf16x8& k, const bf16x8& q, const f32x16& c) {
+      return K_FIRST ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q, c, 0, 0, 0)
+                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, k, c, 0, 0, 0);
+    };
+    const int b = t & 1;
+    const bool more = t + 1 < a.ntiles;  // workgroup-uniform
+    bf16x8 kf[NF];
+    kf[0] = key_frag(b, 0);
+    kf[1] = key_frag(b, 1);
+    kf[2] = key_frag(b, 2);
+    kf[3] = key_frag(b, 3);
+#pragma unroll
+    for (int i = 0; i < 2 * NF; ++i) {
+      const int f = i / 2, x = i % 2;  // fragment, row tile
+      s[x] = mfma(kf[f], qh[x][f / 2], f ? s[x] : f32x16{});
+      if constexpr (QP == 2)
+        if (f % 2 == 0) s[x] = mfma(kf[f], ql[x][f / 2], s[x]);
+#pragma unroll
+      for (int u = 0; u < PER; ++u) ride(PER * i + u);
+      if (x == 0 && f + 4 < NF) kf[f + 4] = key_frag(b, f + 4);
+      if (i % EVERY == 0 && more) issue_part(t + 1, i / EVERY);
 
-  // ---- pass 1: LSE of every row over all pooled keys (S^T = K Q^T, lane = row)
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-  fetch_tile<D>(a, h, 0, kv);
-  if constexpr (NBUF == 2) {
-    stage_tile<D>(kv, ktile);
-    __syncthreads();
-    if (a.ntiles > 1) fetch_tile<D>(a, h, 1, kv);
-  }
-  for (int t = 0; t < a.ntiles; ++t) {
-    const uint16_t* kt = ktile + (NBUF == 2 ? (t & 1) * TILE : 0);
-    if constexpr (NBUF == 1) {
-      __syncthreads();
-      stage_tile<D>(kv, ktile);
-      __syncthreads();
-      if (t + 1 < a.ntiles) fetch_tile<D>(a, h, t + 1, kv);
     }
-    f32x16 acc[2] = {};
+  };
+  // The exponentials of a tile's 32 scores per lane (row tile e / 16, element e % 16) as a
+  // stream of 34 slots: slot i forms the exponent of score i, takes the exponential of
+  // score i - 1 and adds that of score i - 2, so that no op of a slot waits for another.
+  float tq[32], uq[32];
+  auto slot = [&](const f32x16 (&s)[2], int i, auto exponent, float (&sum)[2]) {
+    if (i < 32) {
+      tq[i] = exponent(s[i / 16][i % 16], i);
+      asm volatile("" : "+v"(tq[i]));
+    }
+    if (i >= 1 && i <= 32) {
+      uq[i - 1] = __builtin_amdgcn_exp2f(tq[i - 1]);
+      asm volatile("" : "+v"(uq[i - 1]));
+    }
+    if (i >= 2) {
+      sum[(i - 2) / 16] += uq[i - 2];
+      asm volatile("" : "+v"(sum[(i - 2) / 16]));
+    }
+  };
+
+  // ---- pass 1: LSE of every row over all pooled keys (S^T = K Q^T, lane = row); s[x][i] is
+  // key t*64 + 32 kq + 8 (i/4) + 4 half + i%4 against row 64 rh + 32 x + lane%32; the running
+  // max is kept in raw (unscaled) units, scale > 0
+  float m_run[2] = {kPNoMax, kPNoMax}, l_run[2] = {0.f, 0.f}, off[2];
+  auto new_max = [&](const f32x16 (&s)[2]) {
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8 kh = key_frag<D>(kt, 0, kk, krow, half), kl = key_frag<D>(kt, 1, kk, krow, half);
+    for (int x = 0; x < 2; ++x) {
+      float m0 = fmaxf(m_run[x], s[x][0]), m1 = s[x][1];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[s][kk], acc[s], 0, 0, 0);
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[s][kk], acc[s], 0, 0, 0);
-        if constexpr (QP == 2) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql[s][kk], acc[s], 0, 0, 0);
+      for (int i = 2; i < 16; i += 2) {
+        m0 = fmaxf(m0, s[x][i]);
+        m1 = fmaxf(m1, s[x][i + 1]);
       }
+      m0 = fmaxf(m0, m1);
+      l_run[x] *= __builtin_amdgcn_exp2f(c2 * (m_run[x] - m0));
+      m_run[x] = m0;
+      off[x] = -c2 * m0;
     }
-    // acc[s][i]: key t*64 + 32 kq + 8 (i/4) + 4 half + i%4 against row 64 rh + 32 s + lane%32;
-    // the running max is kept in raw (unscaled) units, scale > 0
+  };
+  auto exponent1 = [&](float s, int i) { return fmaf(s, c2, off[i / 16]); };
+  auto mask_tail = [&](int t, f32x16 (&s)[2]) {
     if (t * kPKeys + kPKeys > a.nb) {  // workgroup-uniform: only the last tile is partial
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int b = t * kPKeys + 32 * kq + 8 * (i / 4) + 4 * half + i % 4;
-        if (b >= a.nb) acc[0][i] = acc[1][i] = -INFINITY;
+        if (b >= a.nb) s[0][i] = s[1][i] = -INFINITY;
       }
     }
+  };
+  auto add_tile = [&](const f32x16 (&s)[2]) {
+    new_max(s);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      float mx = acc[s][0];
-#pragma unroll
-      for (int i = 1; i < 16; ++i) mx = fmaxf(mx, acc[s][i]);
-      if (mx > -INFINITY) {
-        const float mnew = fmaxf(m_run[s], mx), off = -c2 * mnew;
-        float sum = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(fmaf(acc[s][i], c2, off));
-        l_run[s] = l_run[s] * __builtin_amdgcn_exp2f(c2 * (m_run[s] - mnew)) + sum;
-        m_run[s] = mnew;
-      }
+    for (int i = 0; i < 34; ++i) slot(s, i, exponent1, l_run);
+  };
+  auto step1 = [&](int t, const f32x16 (&prev)[2], f32x16 (&s)[2]) {
+    if constexpr (PIPE) {
+      new_max(prev);
+      products(std::true_type{}, t, s, [&](int i) { slot(prev, i, exponent1, l_run); });
+      slot(prev, 32, exponent1, l_run);
+      slot(prev, 33, exponent1, l_run);
+      mask_tail(t, s);
+    } else {
+      products(std::true_type{}, t, s, [](int) {});
+      mask_tail(t, s);
+      add_tile(s);
     }
-    if constexpr (NBUF == 2) {
-      if (t + 1 < a.ntiles) stage_tile<D>(kv, ktile + ((t + 1) & 1) * TILE);
-      __syncthreads();
-      if (t + 2 < a.ntiles) fetch_tile<D>(a, h, t + 2, kv);
+    step_barrier();
+  };
+  f32x16 sa[2] = {none, none}, sb[2];
+  step_barrier();
+  for (int t = 0; t < a.ntiles; t += 2) {
+    step1(t, sa, sb);
+    if (t + 1 < a.ntiles) {
+      step1(t + 1, sb, sa);
+    } else if constexpr (PIPE) {
+      sa[0] = sb[0];
+      sa[1] = sb[1];
     }
   }
+  if constexpr (PIPE) add_tile(sa);
+  if constexpr (!MULTI) issue(0);  // every wave is past its reads of the first pass
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     lse_merge(m_run[s], l_run[s], __shfl_xor(m_run[s], 32), __shfl_xor(l_run[s], 32), c2);
@@ -305,56 +390,88 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   }
   __syncthreads();
 
-  // ---- pass 2: exp(u - LSE) summed over each segment's rows (S = Q K^T, lane = key)
+  // ---- pass 2: exp(u - LSE) summed over each segment's rows (S = Q K^T, lane = key); s[x][i]
+  // is row 64 rh + 32 x + 8 (i/4) + 4 half + i%4 against key t*64 + krow
   float lr[2][16];
 #pragma unroll
   for (int s = 0; s < 2; ++s)
 #pragma unroll
     for (int i = 0; i < 16; ++i) lr[s][i] = lse2[64 * rh + 32 * s + 8 * (i / 4) + 4 * half + i % 4];
-  const int ngroups = MULTI ? min(a.gps, a.R - seg0) : 1;
-  float* const part_row = a.part + (static_cast<int64_t>(h) * a.nseg + seg0) * a.nb;
-  fetch_tile<D>(a, h, 0, kv);
-  if constexpr (NBUF == 2) {
-    stage_tile<D>(kv, ktile);
-    __syncthreads();
-    if (a.ntiles > 1) fetch_tile<D>(a, h, 1, kv);
-  }
-  for (int t = 0; t < a.ntiles; ++t) {
-    const uint16_t* kt = ktile + (NBUF == 2 ? (t & 1) * TILE : 0);
-    if constexpr (NBUF == 1) {
-      __syncthreads();
-      stage_tile<D>(kv, ktile);
-      __syncthreads();
-      if (t + 1 < a.ntiles) fetch_tile<D>(a, h, t + 1, kv);
-    }
-    f32x16 acc[2] = {};
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      const bf16x8 kh = key_frag<D>(kt, 0, kk, krow, half), kl = key_frag<D>(kt, 1, kk, krow, half);
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh[s][kk], kh, acc[s], 0, 0, 0);
-        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh[s][kk], kl, acc[s], 0, 0, 0);
-        if constexpr (QP == 2) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql[s][kk], kh, acc[s], 0, 0, 0);
-      }
-    }
-    // acc[s][i]: row 64 rh + 32 s + 8 (i/4) + 4 half + i%4 against key t*64 + krow
-    const int b0 = t * kPKeys;
-    if constexpr (!MULTI) {
-      // the key sums of tile t go to buffer t & 1; those of tile t - 1, written
-      // before the last barrier, are added and stored now
-      float v = 0.f;
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v += __builtin_amdgcn_exp2f(fmaf(acc[s][i], c2, -lr[s][i]));
+  if constexpr (!MULTI) {
+    float* const part_row = a.part + (static_cast<int64_t>(h) * a.nseg + seg0) * a.nb;
+    auto exponent2 = [&](float s, int i) { return fmaf(s, c2, -lr[i / 16][i % 16]); };
+    // tile t's key sums of the two row halves meet in red buffer t & 1, written before one
+    // barrier and read after it
+    auto put = [&](int t, const float (&sum)[2]) {
+      float v = sum[0] + sum[1];
       v += __shfl_xor(v, 32);
       if (half == 0) red[(t & 1) * 2 * kPKeys + rh * kPKeys + krow] = v;
-      if (t > 0 && tid < kPKeys && b0 - kPKeys + tid < a.nb) {
-        const float* r = red + ((t - 1) & 1) * 2 * kPKeys;
-        part_row[b0 - kPKeys + tid] = r[tid] + r[kPKeys + tid];
+    };
+    auto store = [&](int t) {
+      const int b = t * kPKeys + tid;
+      if (t >= 0 && tid < kPKeys && b < a.nb) {
+        const float* r = red + (t & 1) * 2 * kPKeys;
+        part_row[b] = r[tid] + r[kPKeys + tid];
       }
-    } else {
+    };
+    auto step2 = [&](int t, const f32x16 (&prev)[2], f32x16 (&s)[2]) {
+      float sum[2] = {0.f, 0.f};
+      if constexpr (PIPE) {
+        store(t - 2);
+        products(std::false_type{}, t, s, [&](int i) { slot(prev, i, exponent2, sum); });
+        slot(prev, 32, exponent2, sum);
+        slot(prev, 33, exponent2, sum);
+        if (t > 0) put(t - 1, sum);
+      } else {
+        store(t - 1);
+        products(std::false_type{}, t, s, [](int) {});
+#pragma unroll
+        for (int i = 0; i < 34; ++i) slot(s, i, exponent2, sum);
+        put(t, sum);
+      }
+      step_barrier();
+    };
+    sa[0] = sa[1] = none;
+    step_barrier();
+    for (int t = 0; t < a.ntiles; t += 2) {
+      step2(t, sa, sb);
+      if (t + 1 < a.ntiles) {
+        step2(t + 1, sb, sa);
+      } else if constexpr (PIPE) {
+        sa[0] = sb[0];
+        sa[1] = sb[1];
+      }
+    }
+    if constexpr (PIPE) {
+      store(a.ntiles - 2);
+      float sum[2] = {0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 34; ++i) slot(sa, i, exponent2, sum);
+      put(a.ntiles - 1, sum);
+      step_barrier();
+    }
+    store(a.ntiles - 1);
+  } else {
+    const int ngroups = min(a.gps, a.R - seg0);
+    u32x4 kv[LPT];
+    fetch_tile<D>(a, h, 0, kv);
+    for (int t = 0; t < a.ntiles; ++t) {
+      __syncthreads();
+      stage_tile<D>(kv, lds);
+      __syncthreads();
+      if (t + 1 < a.ntiles) fetch_tile<D>(a, h, t + 1, kv);
+      f32x16 acc[2] = {};
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 kh = key_frag(0, 2 * kk), kl = key_frag(0, 2 * kk + 1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh[s][kk], kh, acc[s], 0, 0, 0);
+          acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qh[s][kk], kl, acc[s], 0, 0, 0);
+          if constexpr (QP == 2) acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ql[s][kk], kh, acc[s], 0, 0, 0);
+        }
+      }
+      const int b0 = t * kPKeys;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -375,18 +492,6 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
               live ? score_key(sum / static_cast<float>(r_end - j * a.G)) : 0u;
         }
       }
-    }
-    if constexpr (NBUF == 2) {
-      if (t + 1 < a.ntiles) stage_tile<D>(kv, ktile + ((t + 1) & 1) * TILE);
-      __syncthreads();
-      if (t + 2 < a.ntiles) fetch_tile<D>(a, h, t + 2, kv);
-    }
-  }
-  if constexpr (!MULTI) {  // the last tile's key sums, written before the loop's last barrier
-    const int t = a.ntiles - 1, b = t * kPKeys + tid;
-    if (tid < kPKeys && b < a.nb) {
-      const float* r = red + (t & 1) * 2 * kPKeys;
-      part_row[b] = r[tid] + r[kPKeys + tid];
     }
   }
 }

@@ -6,8 +6,9 @@ import pytest
 import torch
 
 import oracle
-from paper_2605_30519_amd import omnimem_dense_attn, omnimem_sparse_attn, synth
-from parity import check_bf16, check_f32, check_lse, say
+from paper_2605_30519_amd import (SCORE_PROB, CompressedCache, omnimem_compress_chunk, omnimem_dense_attn,
+                                  omnimem_select_compressed, omnimem_sparse_attn, synth)
+from parity import check_bf16, check_f32, check_lse, check_selection, say
 
 pytestmark = pytest.mark.gpu
 NAN = float("nan")
@@ -132,3 +133,29 @@ def test_key_streams(dev, d, H, Lq, G, K, streams):
     check((out, lse), ref, torch.bfloat16, "sparse")
     ref = oracle.dense_attn(q, k, v, B, 0, n, scale, resident=resident, hs=hs, qs=qs)
     check((dout, dlse), ref, torch.bfloat16, "dense")
+
+
+# Probability scores over one, two and three 64-key tiles, exactly full and one key over,
+# in both slice modes; what the compressed cache holds past the history is NaN.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,n,G", [(128, 64, 200), (128, 65, 200), (128, 128, 70), (64, 129, 200), (64, 63, 70),
+                                   (64, 64, 15), (128, 129, 15), (128, 1, 200)])
+def test_prob_tiles(dev, d, n, G, dtype):
+    say(f"prob tiles d={d} keys={n} G={G} {dtype}")
+    H, S, B, Lq, K = 2, 64, 64, 200, 5
+    q, k, v, cache, _ = make(dev, H, d, S, Lq, B, n, dtype, n + d)
+    cc = CompressedCache.allocate(cache, n + 70)
+    for t in (cc.k_mean, cc.k_pages, cc.v_pages) + ((cc.k_lo,) if cc.k_lo is not None else ()):
+        t.fill_(NAN)
+    for c in range(n):
+        omnimem_compress_chunk(cache, c, cc)
+    sel = omnimem_select_compressed(cache, cc, q.to(dev), K, G, 0, 0, d ** -0.5, score_mode=SCORE_PROB)
+    kbar = k.double().mean(dim=1).permute(1, 0, 2).contiguous().numpy()
+    ref = oracle.select_prob(q, kbar, n, 1, K, G, 0, 0, d ** -0.5, want_all_scores=True)
+    idx, cnt, score = sel.idx.cpu().numpy(), sel.cnt.cpu().numpy(), sel.score.cpu().numpy()
+    check_selection(idx, cnt, ref)
+    for h in range(H):
+        for r in range(idx.shape[1]):
+            c = int(cnt[h, r])
+            want = ref["all_scores"][h, r, idx[h, r, :c]]
+            assert (np.abs(score[h, r, :c] - want) <= 1e-4 * want).all()
