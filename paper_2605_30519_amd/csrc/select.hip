@@ -346,12 +346,23 @@ __global__ __launch_bounds__(kThreads) void k_score(const float* __restrict__ kb
   }
 }
 
-// Score keys for few groups (R <= kInlineGroups) from stored pooled keys: one wave
-// per run of kScoreRowsPerWave blocks of a head; lane l holds dimensions
-// [D/64 * l, D/64 * (l + 1)) of every proxy query in registers and of each pooled key
-// row as it is read (one coalesced row read per block), then the dot products are
-// reduced across the wave by shuffles.
-constexpr int kScoreRowsPerWave = 8;
+// Score keys for few groups (R <= kInlineGroups) from stored pooled keys, which it reads
+// once: bound by that read and, on short histories, by the chain of latencies (partial
+// sums of Q, keys, reduction).  A row's 16-byte pieces lie on D / 4 lanes, and a wave has
+// kScoreLoads whole-wave loads of consecutive rows in flight (16: 9.1 us where 8 take
+// 6.6).  The loads' dot products are reduced together: each exchange step halves the
+// values a lane carries while it sums, so 8 values over 32 lanes take 9 exchanges, not 40.
+// The proxy query is summed once per workgroup: when every wave summed it, the reads of
+// the same few lines by 3,360 waves took more than the keys.  12 heads, d = 128, kernel
+// time: 4,440 blocks 15.3 -> 6.6 us (27 MB), 1,480 blocks 10.1 -> 5.0 us.
+constexpr int kScoreLoads = 8;
+
+template <int D>
+struct ScoreRows {
+  static constexpr int LANES = D / 4;                 // lanes per row
+  static constexpr int PER_LOAD = kWave / LANES;      // rows per load
+  static constexpr int PER_WAVE = kScoreLoads * PER_LOAD;
+};
 
 template <int D, int NR>
 __global__ __launch_bounds__(kThreads) void k_score_rows(const float* __restrict__ kbar, int64_t kbar_stride,
@@ -359,43 +370,65 @@ __global__ __launch_bounds__(kThreads) void k_score_rows(const float* __restrict
                                                          const int32_t* __restrict__ page_table, int64_t pt_stride,
                                                          int64_t num_pages, int nb, int nbp, int first_excluded, int R,
                                                          float scale, uint32_t* __restrict__ keys) {
-  constexpr int PL = D / kWave;  // dimensions per lane: 2 (d = 128) or 1 (d = 64)
+  using W = ScoreRows<D>;
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, h = blockIdx.y;
-  const int first = (blockIdx.x * (kThreads / kWave) + wave) * kScoreRowsPerWave;
-  float q[NR][PL];
+  const int first = (blockIdx.x * (kThreads / kWave) + wave) * W::PER_WAVE;
+  const int c = lane % W::LANES, sub = lane / W::LANES;
+  // the proxy queries, once per workgroup: a thread's partials are asked for before the
+  // keys, so that their wait leaves the keys in flight
+  __shared__ __attribute__((aligned(16))) float qs[NR][D];
+  float mean[(NR * D + kThreads - 1) / kThreads];
+#pragma unroll
+  for (int u = 0; u < (NR * D + kThreads - 1) / kThreads; ++u) {
+    const int i = threadIdx.x + u * kThreads;
+    float v[1] = {0.f};
+    if (i < R * D) proxy_cols<1>(qpart, h, i / D, R, nsplit, D, i % D, lq, G, v);
+    mean[u] = v[0];
+  }
+  // load i holds rows first + PER_LOAD i + sub (rows past the end read the last one)
+  float4 k[kScoreLoads];
+#pragma unroll
+  for (int i = 0; i < kScoreLoads; ++i) {
+    const int b = min(first + W::PER_LOAD * i + sub, nb - 1);
+    k[i] = *reinterpret_cast<const float4*>(kbar + (static_cast<int64_t>(h) * kbar_stride + b) * D + 4 * c);
+  }
+  // the row whose score this lane ends up with: bits 2:0 of its load's number, highest
+  // first, are the lane's bits LANES / 2, LANES / 4, LANES / 8
+  const int mine = (c / (W::LANES / 2) % 2) * 4 + (c / (W::LANES / 4) % 2) * 2 + c / (W::LANES / 8) % 2;
+  const int b = first + W::PER_LOAD * mine + sub;
+  const int32_t page = page_table != nullptr && b < nb ? page_table[static_cast<int64_t>(h) * pt_stride + b] : 0;
+  const bool live = b < first_excluded && page >= 0 && (page_table == nullptr || page < num_pages);
+#pragma unroll
+  for (int u = 0; u < (NR * D + kThreads - 1) / kThreads; ++u) {
+    const int i = threadIdx.x + u * kThreads;
+    if (i < R * D) qs[i / D][i % D] = mean[u];
+  }
+  __syncthreads();
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    float v[PL];
+    if (r >= R) break;
+    const float4 q = *reinterpret_cast<const float4*>(&qs[r][4 * c]);
+    float v[kScoreLoads];
 #pragma unroll
-    for (int j = 0; j < PL; ++j) v[j] = 0.f;
-    if (r < R) proxy_cols<PL>(qpart, h, r, R, nsplit, D, PL * lane, lq, G, v);
+    for (int i = 0; i < kScoreLoads; ++i)
+      v[i] = fmaf(q.w, k[i].w, fmaf(q.z, k[i].z, fmaf(q.y, k[i].y, q.x * k[i].x)));
+    int n = kScoreLoads;
 #pragma unroll
-    for (int j = 0; j < PL; ++j) q[r][j] = v[j];
-  }
-  float k[kScoreRowsPerWave][PL];  // every row's loads in flight before the products
+    for (int m = W::LANES / 2; m >= 1; m >>= 1) {
+      if (n > 1) {  // keep one half of the values, hand the other to the lane that keeps it
+        n /= 2;
+        const bool upper = c & m;
 #pragma unroll
-  for (int i = 0; i < kScoreRowsPerWave; ++i) {
-    const int b = first + i;
-#pragma unroll
-    for (int j = 0; j < PL; ++j)
-      k[i][j] = b < nb ? kbar[(static_cast<int64_t>(h) * kbar_stride + b) * D + PL * lane + j] : 0.f;
-  }
-#pragma unroll
-  for (int i = 0; i < kScoreRowsPerWave; ++i) {
-    const int b = first + i;
-    if (b >= nb) break;
-    const int32_t p = page_table != nullptr ? page_table[static_cast<int64_t>(h) * pt_stride + b] : 0;
-    const bool live = b < first_excluded && p >= 0 && (page_table == nullptr || p < num_pages);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (r >= R) break;
-      float dot = 0.f;
-#pragma unroll
-      for (int j = 0; j < PL; ++j) dot = fmaf(q[r][j], k[i][j], dot);
-#pragma unroll
-      for (int m = 1; m < kWave; m <<= 1) dot += __shfl_xor(dot, m);
-      if (lane == 0) keys[(static_cast<int64_t>(h) * R + r) * nbp + b] = live ? score_key(scale * dot) : 0u;
+        for (int i = 0; i < n; ++i) {
+          const float keep = upper ? v[n + i] : v[i], give = upper ? v[i] : v[n + i];
+          v[i] = keep + __shfl_xor(give, m);
+        }
+      } else {
+        v[0] += __shfl_xor(v[0], m);
+      }
     }
+    if (c % (W::LANES / 8) == 0 && b < nb)
+      keys[(static_cast<int64_t>(h) * R + r) * nbp + b] = live ? score_key(scale * v[0]) : 0u;
   }
 }
 
@@ -1249,7 +1282,7 @@ template <int D>
 hipError_t launch_score(const CacheGeom& g, const SelectPlan& p, const float* kbar, int64_t kbar_stride,
                         const float* qpart, int nbp, uint32_t* keys, hipStream_t stream) {
   if (p.R <= kInlineGroups) {
-    const int waves = (g.nb + kScoreRowsPerWave - 1) / kScoreRowsPerWave;
+    const int waves = (g.nb + ScoreRows<D>::PER_WAVE - 1) / ScoreRows<D>::PER_WAVE;
     const dim3 grid((waves + kThreads / kWave - 1) / (kThreads / kWave), g.H);
     if (p.R == 1)
       return launch_kernel(k_score_rows<D, 1>, grid, dim3(kThreads), 0, stream, kbar, kbar_stride, qpart, p.qsplit,

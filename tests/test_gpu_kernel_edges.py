@@ -159,3 +159,23 @@ def test_prob_tiles(dev, d, n, G, dtype):
             c = int(cnt[h, r])
             want = ref["all_scores"][h, r, idx[h, r, :c]]
             assert (np.abs(score[h, r, :c] - want) <= 1e-4 * want).all()
+
+
+# Mean-logit scores from the pooled keys for one to four groups: 16 (d = 128) or 32 rows per
+# wave, four waves per workgroup; every block selected, so that every score is compared.
+@pytest.mark.parametrize("d,n,G", [(128, 1, 100), (128, 15, 100), (128, 16, 25), (128, 17, 34), (128, 65, 100),
+                                   (64, 31, 100), (64, 33, 25), (64, 129, 50)])
+def test_pooled_score_rows(dev, d, n, G):
+    say(f"pooled score rows d={d} blocks={n} G={G}")
+    H, S, B, Lq = 3, 64, 64, 100
+    q, k, v, cache, resident = make(dev, H, d, S, Lq, B, n, torch.bfloat16, 5 * n + d, nonresident=[n // 2] if n > 2 else [])
+    cc = CompressedCache.allocate(cache, n)
+    for c in range(n):
+        omnimem_compress_chunk(cache, c, cc)
+    sel = omnimem_select_compressed(cache, cc, q.to(dev), n + 1, G, 0, 0, d ** -0.5)
+    ref = oracle.select(q, k, B, n + 1, G, 0, 0, d ** -0.5, resident=resident, want_all_scores=True)
+    idx, cnt, score = sel.idx.cpu().numpy(), sel.cnt.cpu().numpy(), sel.score.cpu().numpy()
+    check_selection(idx, cnt, ref)
+    want = np.where(ref["idx"] >= 0, ref["score"], 0.0)
+    # fp32 sums of d products: d * 2^-24 of sum |q k| / sqrt(d), a few units here
+    assert np.abs(np.where(np.isfinite(score), score, 0.0) - want).max() <= 2e-5
