@@ -192,6 +192,8 @@ def lib():
     """The loaded libomnimem.so.  Builds it if it has never been built; there is no
     fallback: without the HIP library nothing in this module runs."""
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             if not _build.is_built():
@@ -254,19 +256,20 @@ class PagedKVCache:
         """C descriptor; `num_chunks` < n exposes only the oldest chunks (a shorter history);
         with_table=False passes a NULL page table (selection from pooled keys only)."""
         kp, vp, pt = self.k_pages, self.v_pages, self.page_table
-        if kp.dtype not in _DTYPES or vp.dtype != kp.dtype:
-            raise TypeError(f"unsupported page dtype {kp.dtype}")
-        for t in (kp, vp, pt):
-            if not t.is_contiguous():
-                raise ValueError("cache tensors must be contiguous")
-        if pt.dtype != torch.int32:
+        kdt, shape, pt_shape = kp.dtype, kp.shape, pt.shape
+        code = _DTYPES.get(kdt)
+        if code is None or vp.dtype is not kdt:
+            raise TypeError(f"unsupported page dtype {kdt}")
+        if not (kp.is_contiguous() and vp.is_contiguous() and pt.is_contiguous()):
+            raise ValueError("cache tensors must be contiguous")
+        if pt.dtype is not torch.int32:
             raise TypeError("page_table must be int32")
-        if kp.dim() != 4 or vp.shape != kp.shape:
+        if len(shape) != 4 or vp.shape != shape:
             raise ValueError("k_pages and v_pages must share one [num_pages, H, B, d] shape")
-        num_pages, H, B, d = (int(x) for x in kp.shape)
+        num_pages, H, B, d = shape
         bpc = -(-self.chunk_tokens // B)
-        pt_shape = tuple(pt.shape)
-        if not (len(pt_shape) == 2 or (len(pt_shape) == 3 and pt_shape[0] == H)) or pt_shape[-1] != bpc:
+        dims = len(pt_shape)
+        if not (dims == 2 or (dims == 3 and pt_shape[0] == H)) or pt_shape[-1] != bpc:
             raise ValueError(f"page_table must be [n, {bpc}] or [{H}, n, {bpc}] (blocks per chunk)")
         _on_gpu(kp, v_pages=vp, page_table=pt)
         total = pt_shape[-2]
@@ -274,8 +277,8 @@ class PagedKVCache:
         if n > total:
             raise ValueError("num_chunks exceeds the page table")
         return omnimem_kv_cache_t(
-            _DTYPES[kp.dtype], H, d, B, self.chunk_tokens, n, num_pages, kp.data_ptr(), vp.data_ptr(),
-            pt.data_ptr() if with_table else None, total * bpc if len(pt_shape) == 3 else 0)
+            code, H, d, B, self.chunk_tokens, n, num_pages, kp.data_ptr(), vp.data_ptr(),
+            pt.data_ptr() if with_table else None, total * bpc if dims == 3 else 0)
 
 
 def _current_raw_stream():
@@ -287,16 +290,19 @@ def _current_raw_stream():
         return torch.cuda.current_stream().cuda_stream
 
 
+# Streams and tensors as plain addresses (None = NULL): the functions' declared
+# argument types convert them.
+
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(_current_raw_stream())
+        return _current_raw_stream()
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(None)
+    return t.data_ptr() if t is not None else None
 
 
 def _check(status: int, what: str):
@@ -322,7 +328,10 @@ def _on_gpu(like: torch.Tensor, like_name: str = "the cache", **tensors):
     """Every given tensor (None = absent) lives on the GPU that holds `like`."""
     if like.is_cuda:  # the common case, without building any message
         dev = like.get_device()
-        if all(t is None or (t.is_cuda and t.get_device() == dev) for t in tensors.values()):
+        for t in tensors.values():
+            if t is not None and not (t.is_cuda and t.get_device() == dev):
+                break
+        else:
             return
     _need(like.is_cuda, f"{like_name} must live on a GPU")
     for name, t in tensors.items():
@@ -333,8 +342,9 @@ def _on_gpu(like: torch.Tensor, like_name: str = "the cache", **tensors):
 
 
 def _check_tensor(name: str, t, shape, dtype):
-    if isinstance(t, torch.Tensor) and t.dtype == dtype and tuple(t.shape) == tuple(shape) and t.is_contiguous():
-        return  # the common case, without building any message
+    # the common case, without building any message (shape: a tuple, as torch.Size is one)
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return
     _need(isinstance(t, torch.Tensor), f"{name} must be a tensor")
     _need(tuple(t.shape) == tuple(shape), f"{name} must have shape {tuple(shape)}, not {tuple(t.shape)}")
     _need(t.dtype == dtype, f"{name} must be {dtype}, not {t.dtype}")
@@ -344,13 +354,14 @@ def _check_tensor(name: str, t, shape, dtype):
 def _check_q(cache: "PagedKVCache", q) -> int:
     """q: [lq, H, d] in the cache's dtype, contiguous.  Returns lq."""
     _need(isinstance(q, torch.Tensor) and q.dim() == 3, "q must be a [lq, H, d] tensor")
-    lq = int(q.shape[0])
-    _check_tensor("q", q, (lq, cache.num_heads, cache.head_dim), cache.dtype)
+    pages = cache.k_pages
+    lq, (_, H, _, d) = q.shape[0], pages.shape
+    _check_tensor("q", q, (lq, H, d), pages.dtype)
     return lq
 
 
 def _check_outputs(q: torch.Tensor, out, lse):
-    lq, H, d = (int(s) for s in q.shape)
+    lq, H, d = q.shape
     if out is not None:
         _check_tensor("out", out, (lq, H, d), q.dtype)
     if lse is not None:
@@ -360,10 +371,10 @@ def _check_outputs(q: torch.Tensor, out, lse):
 def _check_lists(q: torch.Tensor, idx, cnt, group_size: int) -> int:
     """idx [H, R, K] and cnt [H, R] int32 for R = ceil(lq / group_size).  Returns K."""
     _need(int(group_size) >= 1, "group_size must be >= 1")
-    lq, H = int(q.shape[0]), int(q.shape[1])
+    lq, H, _ = q.shape
     R = -(-lq // int(group_size))
     _need(isinstance(idx, torch.Tensor) and idx.dim() == 3, "idx must be an [H, R, K] tensor")
-    K = int(idx.shape[-1])
+    K = idx.shape[-1]
     _need(K >= 1, "idx must hold at least one entry per row")
     _check_tensor("idx", idx, (H, R, K), torch.int32)
     _check_tensor("cnt", cnt, (H, R), torch.int32)
@@ -372,8 +383,9 @@ def _check_lists(q: torch.Tensor, idx, cnt, group_size: int) -> int:
 
 def _check_workspace(ws, need: int, like: torch.Tensor):
     _need(isinstance(ws, torch.Tensor) and ws.dim() == 1, "workspace must be a 1-D uint8 tensor")
-    _check_tensor("workspace", ws, (int(ws.shape[0]),), torch.uint8)
-    _need(ws.numel() >= need, f"workspace holds {ws.numel()} bytes, {need} needed")
+    _check_tensor("workspace", ws, (ws.shape[0],), torch.uint8)
+    if ws.numel() < need:
+        raise ValueError(f"workspace holds {ws.numel()} bytes, {need} needed")
     _on_gpu(like, workspace=ws)
 
 
@@ -447,7 +459,6 @@ def omnimem_select(cache: PagedKVCache, q: torch.Tensor, top_k: int, group_size:
         out = Selection(torch.empty((H, R, top_k), dtype=torch.int32, device=dev),
                         torch.empty((H, R), dtype=torch.int32, device=dev),
                         torch.empty((H, R, top_k), dtype=torch.float32, device=dev) if want_score else None, 0)
-    _check_selection_out(out, H, R, int(top_k))
     _on_gpu(cache.k_pages, q=q, idx=out.idx, cnt=out.cnt, score=out.score)
     need = int(lib().omnimem_select_workspace_bytes(ctypes.byref(desc), lq, ctypes.byref(params)))
     if workspace is None:
@@ -588,30 +599,37 @@ class CompressedCache:
 
     def check_against(self, cache: PagedKVCache):
         """The pooled tensors must match the full cache's heads, dim, dtype and GPU."""
-        H, d = cache.num_heads, cache.head_dim
-        tokens = max(self.capacity_chunks * cache.blocks_per_chunk, 1)
-        pages = max(1, -(-tokens // CMP_PAGE_TOKENS))
-        _need(self.block_size == cache.block_size and self.chunk_tokens == cache.chunk_tokens,
+        full = cache.k_pages
+        _, H, B, d = full.shape
+        dtype, k_mean = full.dtype, self.k_mean
+        _need(self.block_size == B and self.chunk_tokens == cache.chunk_tokens,
               "compressed cache geometry differs from the full cache")
-        _need(self.k_mean.dim() == 3, "k_mean must be [H, capacity*Bpc, d]")
-        _check_tensor("k_mean", self.k_mean, (H, int(self.k_mean.shape[1]), d), torch.float32)
-        _need(int(self.k_mean.shape[1]) >= tokens, "k_mean holds fewer pooled tokens than the capacity")
+        tokens = max(self.capacity_chunks * -(-self.chunk_tokens // B), 1)
+        pages = max(1, -(-tokens // CMP_PAGE_TOKENS))
+        _need(k_mean.dim() == 3, "k_mean must be [H, capacity*Bpc, d]")
+        held = k_mean.shape[1]
+        _check_tensor("k_mean", k_mean, (H, held, d), torch.float32)
+        _need(held >= tokens, "k_mean holds fewer pooled tokens than the capacity")
         for name, t in (("cmp k_pages", self.k_pages), ("cmp v_pages", self.v_pages)):
-            _need(t.dim() == 4, f"{name} must be [pages, H, {CMP_PAGE_TOKENS}, d]")
-            _check_tensor(name, t, (int(t.shape[0]), H, CMP_PAGE_TOKENS, d), cache.dtype)
-            _need(int(t.shape[0]) >= pages, f"{name} holds fewer pages than the capacity needs")
-        _check_tensor("cmp page_table", self.page_table, (int(self.page_table.shape[0]),), torch.int32)
+            if t.dim() != 4:
+                raise ValueError(f"{name} must be [pages, H, {CMP_PAGE_TOKENS}, d]")
+            held = t.shape[0]
+            _check_tensor(name, t, (held, H, CMP_PAGE_TOKENS, d), dtype)
+            if held < pages:
+                raise ValueError(f"{name} holds fewer pages than the capacity needs")
+        _check_tensor("cmp page_table", self.page_table, (self.page_table.shape[0],), torch.int32)
         if self.k_lo is not None:
-            _need(cache.dtype == torch.bfloat16, "k_lo exists for bf16 caches only")
-            _check_tensor("cmp k_lo", self.k_lo, tuple(int(x) for x in self.k_pages.shape), torch.bfloat16)
+            _need(dtype is torch.bfloat16, "k_lo exists for bf16 caches only")
+            _check_tensor("cmp k_lo", self.k_lo, self.k_pages.shape, torch.bfloat16)
         _on_gpu(cache.k_pages, k_mean=self.k_mean, cmp_k_pages=self.k_pages, cmp_v_pages=self.v_pages,
                 cmp_page_table=self.page_table, cmp_k_lo=self.k_lo)
 
     def descriptor(self) -> omnimem_cmp_cache_t:
+        kp = self.k_pages
+        pages, H, _, d = kp.shape
         return omnimem_cmp_cache_t(
-            _DTYPES[self.k_pages.dtype], int(self.k_pages.shape[1]), int(self.k_pages.shape[3]), self.block_size,
-            self.chunk_tokens, self.capacity_chunks, self.k_mean.data_ptr(), self.k_pages.data_ptr(),
-            self.v_pages.data_ptr(), self.page_table.data_ptr(), int(self.k_pages.shape[0]),
+            _DTYPES[kp.dtype], H, d, self.block_size, self.chunk_tokens, self.capacity_chunks, self.k_mean.data_ptr(),
+            kp.data_ptr(), self.v_pages.data_ptr(), self.page_table.data_ptr(), pages,
             self.k_lo.data_ptr() if self.k_lo is not None else None)
 
 
@@ -650,7 +668,6 @@ def omnimem_select_compressed(cache: PagedKVCache, cc: CompressedCache, q: torch
         out = Selection(torch.empty((H, R, top_k), dtype=torch.int32, device=dev),
                         torch.empty((H, R), dtype=torch.int32, device=dev),
                         torch.empty((H, R, top_k), dtype=torch.float32, device=dev) if want_score else None, 0)
-    _check_selection_out(out, H, R, int(top_k))
     _on_gpu(cache.k_pages, q=q, idx=out.idx, cnt=out.cnt, score=out.score)
     need = int(lib().omnimem_select_workspace_bytes(ctypes.byref(desc), lq, ctypes.byref(params)))
     if workspace is None:
@@ -692,7 +709,7 @@ def omnimem_gated_combine(o_cmp: Optional[torch.Tensor], o_slc: Optional[torch.T
     """Eq. 1: out = sum_c sigmoid(gate_logits[..., c]) * o_c over the given branches
     (CMP, SLC, SWA); gate_logits [lq, H, 3] float32."""
     ref = next(o for o in (o_cmp, o_slc, o_swa) if o is not None)
-    lq, H, d = (int(s) for s in ref.shape)
+    lq, H, d = ref.shape
     for o in (o_cmp, o_slc, o_swa):
         if o is not None and (o.shape != ref.shape or o.dtype != ref.dtype or not o.is_contiguous()):
             raise ValueError("branch outputs must share shape, dtype and be contiguous")
