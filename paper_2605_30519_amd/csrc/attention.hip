@@ -476,6 +476,33 @@ __device__ __forceinline__ void keep_here(const bf16x8 (&pb)[4], float l) {
 __device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16x8& p) {
   asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(v), "v"(p));
 }
+// The same MFMA with its two wait states filled by the softmax stream's own work, ahead of
+// it: t = s c - m (the exponent of a score), and sum += u (an earlier exponential, taken
+// more than the one wait state a transcendental's result needs before) or the other half's
+// exponent.  The scores were formed an MFMA run earlier, so the VALU reads of MFMA results
+// that the compiler does not see here are far past their hazard.  Against two empty wait
+// states before every MFMA, 12 heads x 4,680 rows x 64 blocks: 113.2 -> 110.5 us; 5 heads x
+// 3 groups x 1,560 rows in two key streams: 64.1 -> 61.7 us.
+__device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16x8& p, float& t, float s, float c,
+                                        float m, float& sum, float u) {
+  asm volatile(
+      "v_fma_f32 %1, %5, %6, -%7\n\tv_add_f32 %2, %2, %8\n\tv_mfma_f32_32x32x16_bf16 %0, %3, %4, %0"
+      : "+a"(acc), "=&v"(t), "+v"(sum)
+      : "v"(v), "v"(p), "v"(s), "v"(c), "v"(m), "v"(u));
+}
+__device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16x8& p, float& t, float s, float c,
+                                        float m) {
+  asm volatile("v_fma_f32 %1, %4, %5, -%6\n\ts_nop 0\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0"
+               : "+a"(acc), "=&v"(t)
+               : "v"(v), "v"(p), "v"(s), "v"(c), "v"(m));
+}
+__device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16x8& p, float& t0, float s0, float m0,
+                                        float& t1, float s1, float m1, float c) {
+  asm volatile(
+      "v_fma_f32 %1, %5, %9, -%6\n\tv_fma_f32 %2, %7, %9, -%8\n\tv_mfma_f32_32x32x16_bf16 %0, %3, %4, %0"
+      : "+a"(acc), "=&v"(t0), "=&v"(t1)
+      : "v"(v), "v"(p), "v"(s0), "v"(m0), "v"(s1), "v"(m1), "v"(c));
+}
 // Sixteen wait states (more than an 8-pass MFMA result needs) before VALU code reads
 // or writes the accumulators; they pass through the asm so that no access moves
 // ahead of it.
@@ -650,9 +677,10 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // Each result goes through an empty asm so that the IR passes keep it in its slot
   // (they would otherwise sink every op next to its first use).  The row sum is taken
   // over the fp32 values.
+  // `formed`, `added`: the exponent, the sum have been taken by the slot's PV MFMA.
   auto soft_slot = [&](const f32x16 (&s)[2], float ms, float& acc, bf16x8 (&pb)[4], float (&tq)[32],
-                       float (&uq)[32], int g) {
-    if (g < 32) {
+                       float (&uq)[32], int g, bool formed = false, bool added = false) {
+    if (g < 32 && !formed) {
       tq[g] = fmaf(s[g / 16][g % 16], c, -ms);
       asm volatile("" : "+v"(tq[g]));
     }
@@ -660,7 +688,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       uq[g - 1] = __builtin_amdgcn_exp2f(tq[g - 1]);
       asm volatile("" : "+v"(uq[g - 1]));
     }
-    if (g >= 2 && g <= 33) {
+    if (g >= 2 && g <= 33 && !added) {
       acc += uq[g - 2];
       asm volatile("" : "+v"(acc));
     }
@@ -851,6 +879,11 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   __builtin_amdgcn_s_waitcnt(vmcnt_only(IN_FLIGHT));
   lds_barrier();
 
+  // The operands of the PV MFMA issued last, held until it has read them: those of a run's
+  // last one until the next iteration's QK run has begun (waiting for it at the run's end
+  // took 1% of a tile, 4% at d = 64).
+  bf16x8 hold_a = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0)), hold_b = hold_a;
+
   // Iteration t (t mod kStages = T, a compile-time constant, as are the stages) with tile
   // t-1's S in (so0, so1) and tile t's formed in (sn0, sn1); consecutive iterations
   // swap the two, so that no S is ever copied.  Returns false after the iteration of
@@ -882,6 +915,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         if (BOTH || i % 2 == 0) soft_slot(so0, ms0, acc0, pb0, tq0, uq0, FIRST + (BOTH ? i : f));
         if (BOTH || i % 2 == 1) soft_slot(so1, ms1, acc1, pb1, tq1, uq1, FIRST + (BOTH ? i : f));
         if (i % 2 == 0 && f + 4 < 2 * KK) kf[f + 4] = k_frag(kst, f + 4);
+        if (i == 1) asm volatile("" ::"v"(hold_a), "v"(hold_b));  // the previous PV run's last operands
         if (i % DMA_EVERY == DMA_AT) issue_part(t2, k_into, v_tile, v_into, i / DMA_EVERY);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -914,27 +948,31 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       // are held (an empty asm use) until the end of the next slot, when it has
       // finished: the compiler, which does not see these MFMAs, would otherwise give
       // the registers to the next value as soon as the MFMA is issued.
-      bf16x8 hold_a = vf[0], hold_b = pb0[0];
 #pragma unroll
       for (int i = 0; i < NRUN; ++i) {
         const int f = i / 2;
         const bf16x8 op_a = vf[f], op_b = i % 2 ? pb1[f / DT] : pb0[f / DT];
-        if (i % 2 == 0) {
-          pv_mfma(o0[f % DT], op_a, op_b);
-          if (f + 3 < 4 * DT) vf[f + 3] = v_frag(vst, f + 3);
-        } else {
-          pv_mfma(o1[f % DT], op_a, op_b);
-        }
+        f32x16& o = i % 2 ? o1[f % DT] : o0[f % DT];
+        const int g = BOTH ? i - 2 : f - 1;  // the slot that rides on this MFMA
+        if (i < 2)
+          pv_mfma(o, op_a, op_b);
+        else if (BOTH)
+          pv_mfma(o, op_a, op_b, tq0[g], sn0[g / 16][g % 16], ms0, tq1[g], sn1[g / 16][g % 16], ms1, c);
+        else if (g < 2)
+          pv_mfma(o, op_a, op_b, i % 2 ? tq1[g] : tq0[g], (i % 2 ? sn1 : sn0)[g / 16][g % 16], c, i % 2 ? ms1 : ms0);
+        else
+          pv_mfma(o, op_a, op_b, i % 2 ? tq1[g] : tq0[g], (i % 2 ? sn1 : sn0)[g / 16][g % 16], c, i % 2 ? ms1 : ms0,
+                  i % 2 ? acc1 : acc0, i % 2 ? uq1[g - 2] : uq0[g - 2]);
+        if (i % 2 == 0 && f + 3 < 4 * DT) vf[f + 3] = v_frag(vst, f + 3);
         if (i >= 2) {
-          if (BOTH || i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, BOTH ? i - 2 : f - 1);
-          if (BOTH || i % 2 == 1) soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, BOTH ? i - 2 : f - 1);
+          if (BOTH || i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, g, true, !BOTH);
+          if (BOTH || i % 2 == 1) soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, g, true, !BOTH);
         }
         if (i > 0) asm volatile("" ::"v"(hold_a), "v"(hold_b));
         hold_a = op_a;
         hold_b = op_b;
         __builtin_amdgcn_sched_barrier(0);
       }
-      asm volatile("s_nop 7\n\ts_nop 3" ::"v"(hold_a), "v"(hold_b));  // the last MFMA's operands
     } else {
       issue(t2, k_into, v_tile, v_into);
     }
@@ -958,6 +996,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       if (!iteration(sb0, sb1, sa0, sa1, std::integral_constant<int, 3>{})) break;
     }
   }
+  asm volatile("s_nop 7\n\ts_nop 3" ::"v"(hold_a), "v"(hold_b));
   __builtin_amdgcn_s_waitcnt(vmcnt_only(0));  // no DMA may land in the stages reused below
   __syncthreads();
 
