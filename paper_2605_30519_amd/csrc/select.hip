@@ -1003,18 +1003,36 @@ __global__ __launch_bounds__(kTopkSmallWaves* kWave) void k_topk_small(const uin
   if (lane == 0) cnt[row] = taken;
 }
 
+// The largest of a value over the 64 lanes of a wave, the same in every lane: four steps
+// inside the rows of 16 lanes and two across them, all on the VALU.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+#define OMNIMEM_DPP_MAX(ctrl) v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), ctrl, 0xf, 0xf, false)))
+  OMNIMEM_DPP_MAX(0x111);  // row_shr:1
+  OMNIMEM_DPP_MAX(0x112);  // row_shr:2
+  OMNIMEM_DPP_MAX(0x114);  // row_shr:4
+  OMNIMEM_DPP_MAX(0x118);  // row_shr:8
+  OMNIMEM_DPP_MAX(0x142);  // row_bcast:15
+  OMNIMEM_DPP_MAX(0x143);  // row_bcast:31
+#undef OMNIMEM_DPP_MAX
+  return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
 // Scores and top-K in one kernel, for many query groups and small K (the small-group
 // setting: groups of G_q rows, K blocks each): no score row is stored.  A workgroup
 // takes 16 groups of one head; its NW waves split the head's blocks, each streaming
-// its share 16 blocks at a time, two tiles ahead.  A tile's 16 x 16 scores come from
-// fp32 MFMA (16x16x4): at step (u, e) lane group j = l / 16 supplies dimension
+// its share 16 blocks at a time through two LDS tiles of its own, the next arriving by DMA
+// while one is scored (read from memory in the operand layout, a load was 64 separate
+// 16-byte pieces for the vector cache).  A tile's 16 x 16 scores come from fp32 MFMA
+// (16x16x4): at step (u, e) lane group j = l / 16 supplies dimension
 // 16 u + 4 j + e of its lane's group (A operand) and block (B operand), so the proxy
-// queries stay in registers and the four lane groups of a block read 64 contiguous
-// bytes of its row per load.  Lane l ends a tile with block b0 + l % 16 scored
+// queries stay in registers.  Lane l ends a tile with block b0 + l % 16 scored
 // against groups 4 j .. 4 j + 3 and keeps, per group, the KM best (key, id) pairs it
-// has seen (ids arrive in increasing order).  The lists meet in LDS, where half a
-// wave per group merges them; ranking and ties are those of k_topk (key, then lower
-// id).
+// has seen (ids arrive in increasing order).  The sorted lists meet in LDS, where a wave
+// per group takes the K winners off their heads; ranking and ties are those of k_topk
+// (key, then lower id).  12 heads x 312 groups x 1,480 blocks, K = 4, kernel time: 36.4 us
+// with operand-layout loads and lists merged by insertion, 32.7 with the tiles by DMA,
+// 28.3 with the heads' merge (a floor of 10 us of MFMAs; inserting takes about 6, a
+// workgroup's start 5).  K = 16, the whole selection from pooled keys: 84 -> 66 us.
 constexpr int kStkGroups = 16;
 
 template <int D, int KM, int NW>
@@ -1024,12 +1042,47 @@ __global__ __launch_bounds__(NW* kWave) void k_score_topk(
     float scale, int K, int32_t* __restrict__ idx, int32_t* __restrict__ cnt, float* __restrict__ score_out) {
   constexpr int DS = D / 4;    // dimensions per lane group
   constexpr int NV = DS / 4;   // 16-byte loads per lane per tile: load u covers dimensions [16 u, 16 u + 16)
-  __shared__ uint64_t cand[kStkGroups][NW * 16 * KM];
+  constexpr int ROW = D * 4, TILE = 16 * ROW;            // bytes per pooled key, per tile
+  constexpr int CPR = D / 4, RPI = kWave / CPR;          // 16-byte chunks per row, rows per DMA instruction
+  constexpr int kCand = kStkGroups * NW * 16 * KM * 8;   // the candidate lists take the tiles' place at the end
+  constexpr int kTiles = NW * 2 * TILE;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kCand > kTiles ? kCand : kTiles];
+  auto cand = reinterpret_cast<uint64_t(*)[NW * 16 * KM]>(lds);
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int col = lane % 16, j = lane / 16;
   // workgroups of one head on one XCD, whose L2 then holds that head's pooled keys
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x), tiles = (R + kStkGroups - 1) / kStkGroups;
   const int h = wg / tiles, g0 = (wg % tiles) * kStkGroups;
+
+  // this wave's blocks [bw0, bw1): share (wave + group tile) mod NW, so that the
+  // workgroups of one head read different rows of its pooled keys at a time
+  const int per = ((nb + NW - 1) / NW + 15) / 16 * 16;
+  const int share = (wave + wg % tiles) % NW;
+  const int bw0 = share * per, bw1 = min(bw0 + per, nb);
+  const int32_t* table = page_table ? page_table + static_cast<int64_t>(h) * pt_stride : nullptr;
+  const float* kh = kbar + static_cast<int64_t>(h) * kbar_stride * D;
+
+  // A tile's DMA: an instruction moves 1 KB of whole rows, lane l the chunk that belongs
+  // at position l of it; chunk c of row r sits at position c ^ r of its row, so that an
+  // operand read (one chunk of 16 rows a pass) touches every bank once.  Rows past the last
+  // block read as zero.
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const uint8_t* const tile0 = lds + wave_s * 2 * TILE;
+  auto fetch = [&](int b0, int buf) {
+    const int rows = min(16, nb - b0);
+    const u32x4 rsrc = buffer_rsrc(kh + static_cast<int64_t>(b0) * D, rows > 0 ? rows * ROW : 0);
+    const int at = (lane / CPR) * ROW + (((lane % CPR) ^ (lane / CPR)) << 4);
+    const uint32_t dst = lds_offset(tile0) + buf * TILE;
+#pragma unroll
+    for (int m = 0; m < TILE / 1024; ++m) dma_16x64(rsrc, (at ^ ((RPI * m) << 4)) + m * 1024, dst + m * 1024);
+  };
+  auto page_of = [&](int b0) { return table ? table[min(b0 + col, nb - 1)] : 0; };
+  // the first tile is on its way before the proxy queries are asked for
+  int page = -1, next = -1;
+  if (bw0 < bw1) {
+    page = page_of(bw0);
+    fetch(bw0, 0);
+  }
 
   // the proxy query of group g0 + col, dimensions 16 u + 4 j + e: its partial sums
   // added in split order, divided by the group's row count
@@ -1067,14 +1120,6 @@ __global__ __launch_bounds__(NW* kWave) void k_score_topk(
     }
   }
 
-  // this wave's blocks [bw0, bw1): share (wave + group tile) mod NW, so that the
-  // workgroups of one head read different rows of its pooled keys at a time
-  const int per = ((nb + NW - 1) / NW + 15) / 16 * 16;
-  const int share = (wave + wg % tiles) % NW;
-  const int bw0 = share * per, bw1 = min(bw0 + per, nb);
-  const int32_t* table = page_table ? page_table + static_cast<int64_t>(h) * pt_stride : nullptr;
-  const float* kh = kbar + static_cast<int64_t>(h) * kbar_stride * D;
-
   uint32_t lk[4][KM];
   int li[4][KM];
 #pragma unroll
@@ -1100,26 +1145,15 @@ __global__ __launch_bounds__(NW* kWave) void k_score_topk(
     lii[0] = gt[0] ? id : lii[0];
   };
 
-  // three tile buffers: tile t is scored while tiles t + 1 and t + 2 are in flight.
-  // A tile's page ids are loaded with it and looked at only when it is scored, so
-  // that no wait for its loads is placed at the fetch.
-  float4 kb0[NV], kb1[NV], kb2[NV];
-  int pg0 = -1, pg1 = -1, pg2 = -1;
-  // Loads are unconditional (rows past the wave's share read a valid row, whose
-  // scores are then not candidates): no branch around them, so the compiler's
-  // waits count the loads still in flight instead of draining them all.
-  auto fetch = [&](int b0, float4 (&dst)[NV], int& page) {
-    const int b = min(b0 + col, nb - 1);
-#pragma unroll
-    for (int u = 0; u < NV; ++u)
-      dst[u] = *reinterpret_cast<const float4*>(kh + static_cast<int64_t>(b) * D + 16 * u + 4 * j);
-    page = table ? table[b] : 0;
-  };
-  // scores of the tile in kv (block b0 + col), four independent MFMA chains
-  auto score_tile = [&](int b0, const float4 (&kv)[NV], int page) {
+  // scores of the tile in buffer buf (block b0 + col), four independent MFMA chains
+  auto score_tile = [&](int b0, int buf, int page) {
     const int b = b0 + col;
     const bool live = b < bw1 && b < first_excluded && page >= 0 && (table == nullptr || page < num_pages);
     f32x4 acc[4] = {};
+    float4 kv[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+      kv[u] = *reinterpret_cast<const float4*>(tile0 + buf * TILE + col * ROW + (((4 * u + j) ^ col) << 4));
 #pragma unroll
     for (int u = 0; u < NV; ++u) {
       acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[4 * u + 0], kv[u].x, acc[0], 0, 0, 0);
@@ -1134,18 +1168,19 @@ __global__ __launch_bounds__(NW* kWave) void k_score_topk(
       insert(lk[i], li[i], live ? score_key(scale * dot) : 0u, b0 + col);
     }
   };
-  fetch(bw0, kb0, pg0);
-  fetch(bw0 + 16, kb1, pg1);
-  for (int b0 = bw0; b0 < bw1; b0 += 48) {
-    fetch(b0 + 32, kb2, pg2);
-    score_tile(b0, kb0, pg0);
-    if (b0 + 16 >= bw1) break;
-    fetch(b0 + 48, kb0, pg0);
-    score_tile(b0 + 16, kb1, pg1);
-    if (b0 + 32 >= bw1) break;
-    fetch(b0 + 64, kb1, pg1);
-    score_tile(b0 + 32, kb2, pg2);
+  for (int b0 = bw0, buf = 0; b0 < bw1; b0 += 16, buf ^= 1) {
+    // tile b0 and its page ids have landed (said in a form that the compiler sees, so that
+    // it places no wait of its own that would count the DMA issued next)
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    asm volatile("" ::: "memory");
+    if (b0 + 16 < bw1) {
+      next = page_of(b0 + 16);
+      fetch(b0 + 16, buf ^ 1);
+    }
+    score_tile(b0, buf, page);
+    page = next;
   }
+  __syncthreads();  // every wave is done with its tiles
 
   // every lane's lists to LDS, per group: candidate (wave, col, t) of group 4 j + i
 #pragma unroll
@@ -1157,60 +1192,57 @@ __global__ __launch_bounds__(NW* kWave) void k_score_topk(
                          : (static_cast<uint64_t>(lk[i][t]) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(li[i][t]));
   __syncthreads();
 
-  // half-wave (32 lanes) per group: each lane keeps the KM best of its share of the
-  // group's NW * 16 * KM candidates, then K rounds of a 32-lane maximum name the
-  // winners (the largest (key, lower id) composite), written in ascending id order
-  constexpr int kPerLane = NW * 16 * KM / 32;
-  const int half = lane / 32, l32 = lane % 32;
-  for (int m = 2 * wave + half; m < kStkGroups; m += 2 * NW) {
-    uint64_t top[KM];
+  // A wave per group: the lanes' lists arrive sorted, so a lane keeps the heads of its one
+  // or two lists, and K rounds of a wave-wide maximum (the key first; among equal keys the
+  // lower id, as its complement) name the winners, whose lists move on.  They are written in
+  // ascending id order.
+  constexpr int kLists = NW * 16 / kWave;  // lists per lane
+  static_assert(kLists * kWave == NW * 16, "whole lists per lane");
+  for (int m = wave_s; m < kStkGroups; m += NW) {
+    const int g = g0 + m;
+    if (g >= R) break;  // wave-uniform
+    uint64_t head[kLists];
+    int at[kLists];
 #pragma unroll
-    for (int t = 0; t < KM; ++t) top[t] = 0ull;
-#pragma unroll
-    for (int c = 0; c < kPerLane; ++c) {
-      uint64_t v = cand[m][l32 + 32 * c];
-      if (v > top[KM - 1]) {
-#pragma unroll
-        for (int t = 0; t < KM; ++t) {  // insertion into the descending list
-          const uint64_t hi = top[t] > v ? top[t] : v, lo = top[t] > v ? v : top[t];
-          top[t] = hi;
-          v = lo;
-        }
-      }
+    for (int n = 0; n < kLists; ++n) {
+      at[n] = (n * kWave + lane) * KM;
+      head[n] = cand[m][at[n]];
     }
-    uint64_t win = 0ull;
+    uint32_t win_key = 0u, win_lo = 0u;
     int taken = 0;
     for (int r = 0; r < K; ++r) {
-      uint64_t best = top[0];
+      uint64_t mine = head[0];
 #pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) {
-        const uint64_t o = __shfl_xor(best, off);
-        best = o > best ? o : best;
-      }
-      if (best == 0ull) break;  // fewer than K candidates (uniform within the half)
-      if (top[0] == best) {
+      for (int n = 1; n < kLists; ++n) mine = head[n] > mine ? head[n] : mine;
+      const uint32_t hi = static_cast<uint32_t>(mine >> 32), lo = static_cast<uint32_t>(mine);
+      const uint32_t key = wave_max_u32(hi);
+      if (key == 0u) break;  // fewer than K candidates
+      const uint32_t low = wave_max_u32(hi == key ? lo : 0u);
+      const uint64_t best = static_cast<uint64_t>(key) << 32 | low;
 #pragma unroll
-        for (int t = 0; t + 1 < KM; ++t) top[t] = top[t + 1];
-        top[KM - 1] = 0ull;
+      for (int n = 0; n < kLists; ++n)
+        if (head[n] == best) {  // one list of one lane: ids differ
+          ++at[n];
+          head[n] = at[n] % KM ? cand[m][at[n]] : 0ull;
+        }
+      if (lane == r) {
+        win_key = key;
+        win_lo = low;
       }
-      if (l32 == r) win = best;
       ++taken;
     }
-    const int g = g0 + m;
-    if (g < R) {
-      const int id = static_cast<int>(~static_cast<uint32_t>(win));
-      int rank = 0;
-      for (int s2 = 0; s2 < taken; ++s2) rank += __shfl(id, half * 32 + s2) < id;
-      const int64_t row = static_cast<int64_t>(h) * R + g;
-      if (l32 < taken) {
-        idx[row * K + rank] = id;
-        if (score_out) score_out[row * K + rank] = key_score(static_cast<uint32_t>(win >> 32));
-      } else if (l32 < K) {
-        idx[row * K + l32] = -1;
-        if (score_out) score_out[row * K + l32] = -INFINITY;
-      }
-      if (l32 == 0) cnt[row] = taken;
+    const int id = static_cast<int>(~win_lo);
+    int rank = 0;
+    for (int s2 = 0; s2 < taken; ++s2) rank += __builtin_amdgcn_readlane(id, s2) < id;
+    const int64_t row = static_cast<int64_t>(h) * R + g;
+    if (lane < taken) {
+      idx[row * K + rank] = id;
+      if (score_out) score_out[row * K + rank] = key_score(win_key);
+    } else if (lane < K) {
+      idx[row * K + lane] = -1;
+      if (score_out) score_out[row * K + lane] = -INFINITY;
     }
+    if (lane == 0) cnt[row] = taken;
   }
 }
 
