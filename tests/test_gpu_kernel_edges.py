@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2605_30519_amd import (SCORE_PROB, CompressedCache, omnimem_compress_chunk, omnimem_dense_attn,
-                                  omnimem_select_compressed, omnimem_sparse_attn, synth)
+                                  omnimem_gated_combine, omnimem_select_compressed, omnimem_sparse_attn, synth)
 from parity import check_bf16, check_f32, check_lse, check_selection, say
 
 pytestmark = pytest.mark.gpu
@@ -179,3 +179,26 @@ def test_pooled_score_rows(dev, d, n, G):
     want = np.where(ref["idx"] >= 0, ref["score"], 0.0)
     # fp32 sums of d products: d * 2^-24 of sum |q k| / sqrt(d), a few units here
     assert np.abs(np.where(np.isfinite(score), score, 0.0) - want).max() <= 2e-5
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+def test_gated_combine_rows(dev, dtype, d):
+    """A workgroup takes 16, 32 or 64 rows (by d and dtype): one row, one less, as many and
+    one more, written over a branch, with the rows behind the last left alone."""
+    per = 256 * 2 * (16 // dtype.itemsize) // d
+    for rows in (1, per - 1, per, per + 1):
+        say(f"gated combine rows={rows} d={d} {dtype}")
+        g = torch.Generator(device=dev).manual_seed(rows)
+        full = [torch.randn((rows + 1, 1, d), generator=g, device=dev).to(dtype) for _ in range(3)]
+        logits = torch.randn((rows, 1, 3), generator=g, device=dev)
+        host_in = [x[:rows].cpu().float().numpy().astype(np.float64) for x in full]
+        behind = full[1][rows:].clone()
+        omnimem_gated_combine(*[x[:rows] for x in full], logits, out=full[1][:rows])
+        torch.cuda.synchronize()
+        want = oracle.gated_combine(*host_in, logits.cpu().numpy())
+        # a few fp32 roundings of the terms, then the result's own
+        bound = 8 * 2.0 ** -24 * oracle.gated_combine(*[np.abs(x) for x in host_in], logits.cpu().numpy())
+        bound += np.abs(want) * (2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8)
+        assert (np.abs(full[1][:rows].cpu().float().numpy() - want) <= bound).all()
+        assert torch.equal(full[1][rows:], behind)
