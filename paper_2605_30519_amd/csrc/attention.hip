@@ -139,10 +139,17 @@ struct AttnLds {
 // the tiles of consecutive groups form one stream, the next tile's K and V always
 // in flight while the current one is computed, across group boundaries too.  K
 // goes from memory straight into registers in the MFMA A-operand layout; V passes
-// through the wave's own LDS tile for the transposing reads.  The next group's list
-// entries are fetched when the walk enters a group, its Q rows with its first tile.
+// through the wave's own LDS tile for the transposing reads.  Lists are read two groups
+// ahead and their pages one, a group's Q rows with its first tile.
 // The arithmetic is that of the 64-row kernel: the same operand layouts, an
 // online softmax, the same rounding.
+// Bound by the gathers where groups fill the waves (12 heads x 312 groups x 4 blocks:
+// 520 MB at 6.0 TB/s), by one wave's chain of loads and a tile's work where they do not.
+// With a count, list and table read in series before a group's first tile, and each load
+// of 16 bytes a branch on its row with its register cleared first, those took 88.8 us and,
+// 3 heads x 104 groups (a wave each), 21.9; now 87.1 and 17.4; groups of 32 rows, 40 heads,
+// 8 blocks 88.5 -> 84.8.  K by whole rows through LDS instead: 102 us, the tile's work then
+// waits for two more trips through LDS.
 constexpr int kGrpWaves = 4;
 
 template <int D>
@@ -155,7 +162,8 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
   constexpr int VLOADS = kTileKeys / VROWS;        // V load instructions per tile
   __shared__ __attribute__((aligned(16))) uint16_t v_all[kGrpWaves * L::V_ELEMS];
 
-  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, half = lane / 32;
+  const int lane = threadIdx.x % kWave, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   uint16_t* const v_lds = v_all + wave * L::V_ELEMS;
   const int total = a.H * a.R;
   const int stride = gridDim.x * kGrpWaves;
@@ -168,28 +176,34 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
   const float c = a.scale * kLog2e;
   const int krow = s_row_perm(lane % 32);
 
-  // ---- the walk over groups and tiles (wave-uniform state; w_* and nx_id per lane)
+  // ---- the walk over groups and tiles (wave-uniform state; w_*, nx_* and far_id per lane).
+  // The lists are read ahead: on entering a group, the next group's pages (nx_page) and the
+  // ids and count of the one after (far_*) are asked for and not waited for, so that no
+  // chain of list and table reads stands before a group's first tile.
   int p_hr = first, p_count = 0, p_base = 0, p_e = 0, p_sub = 0, p_emitted = 0;
-  const int32_t* p_list = nullptr;
   int w_page = -1, w_nvb = 0;  // entry p_base + lane: page (-1: no tile) and valid tokens
-  int nx_id = -1, nx_count = 0;
-  const int32_t* nx_list = nullptr;
+  int nx_id = -1, nx_count = 0, nx_page = -1, far_id = -1, far_count = 0;
 
-  auto group_list = [&](int hr, const int32_t*& list) -> int {
-    int count;
-    resolve_list(a, hr, list, count);
-    return count;
+  // entry `lane` of a group's list, and its count, as memory has them (an entry past the
+  // count is read, never used)
+  auto fetch_ids = [&](int hr, int& id, int& count) {
+    id = -1;
+    count = 0;
+    if (hr >= total) return;
+    count = a.dense_count;
+    if (a.idx) {
+      count = a.cnt[hr];
+      if (lane < a.top_k) id = a.idx[static_cast<int64_t>(hr) * a.top_k + lane];
+    } else {
+      id = a.dense_first + lane;
+    }
   };
-  auto entry_id = [&](const int32_t* list, int count, int e) -> int {
-    if (e >= count) return -1;
-    return list ? list[e] : a.dense_first + e;
-  };
+  auto fetch_page = [&](int hr, int id) -> int { return id >= 0 && id < a.nb ? head_table(a, hr / a.R)[id] : -1; };
   // this lane's entry of the window: its page and valid tokens, or no tile
-  auto resolve_window = [&](int id) {
+  auto set_window = [&](int e, int id, int p) {
     w_page = -1;
     w_nvb = 0;
-    if (id >= 0 && id < a.nb) {
-      const int32_t p = head_table(a, p_hr / a.R)[id];
+    if (e < p_count && id >= 0 && id < a.nb) {
       const int o = id % a.Bpc;
       const int nvb = o == a.Bpc - 1 ? a.S - o * a.B : a.B;
       if (p >= 0 && p < a.num_pages && nvb > 0) {
@@ -198,14 +212,16 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
       }
     }
   };
-  auto prefetch_next_ids = [&]() {
-    const int nhr = p_hr + stride;
-    nx_count = 0;
-    nx_id = -1;
-    if (nhr < total) {
-      nx_count = group_list(nhr, nx_list);
-      nx_id = entry_id(nx_list, nx_count, lane);
-    }
+  // enters group p_hr, whose entries are in nx_*
+  auto enter_group = [&]() {
+    const int most = a.idx ? a.top_k : a.dense_count;
+    p_count = __builtin_amdgcn_readfirstlane(min(max(nx_count, 0), most));
+    p_base = p_e = p_sub = p_emitted = 0;
+    set_window(lane, nx_id, nx_page);
+    nx_id = far_id;
+    nx_count = far_count;
+    nx_page = fetch_page(p_hr + stride, nx_id);
+    fetch_ids(p_hr + 2 * stride, far_id, far_count);
   };
   // output of a group without a single tile: O = 0, lse = -inf
   auto write_empty = [&](int hr) {
@@ -215,10 +231,10 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
           make_uint4(0, 0, 0, 0);
     if (a.lse && lane < rows) a.lse[static_cast<int64_t>(h) * a.lq + g0 + lane] = -INFINITY;
   };
-  // first group: its ids now, then the next group's
-  p_count = group_list(p_hr, p_list);
-  resolve_window(entry_id(p_list, p_count, lane));
-  prefetch_next_ids();
+  fetch_ids(first, nx_id, nx_count);
+  fetch_ids(first + stride, far_id, far_count);
+  nx_page = fetch_page(first, nx_id);
+  enter_group();
 
   // the next tile of the walk: page, (sub-tile << 8) | valid keys, its group, and
   // whether it opens the group; false at the end
@@ -227,7 +243,10 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
       while (p_e < p_count) {
         if (p_e >= p_base + kWave) {  // lists longer than a wave: the next window
           p_base += kWave;
-          resolve_window(entry_id(p_list, p_count, p_base + lane));
+          const int e = p_base + lane;
+          int id = -1;
+          if (e < p_count) id = a.idx ? a.idx[static_cast<int64_t>(p_hr) * a.top_k + e] : a.dense_first + e;
+          set_window(e, id, fetch_page(p_hr, id));
           continue;
         }
         const uint64_t live = __ballot(w_page >= 0) & (~0ull << (p_e - p_base));
@@ -257,47 +276,41 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
       if (p_emitted == 0) write_empty(p_hr);
       p_hr += stride;
       if (p_hr >= total) return false;
-      p_list = nx_list;
-      p_count = nx_count;
-      p_base = p_e = p_sub = p_emitted = 0;
-      resolve_window(nx_id);
-      prefetch_next_ids();
+      enter_group();
     }
   };
 
   // ---- registers of the stream: K of two tiles (current, next), V of the next, Q
   bf16x8 ka[2][KK], kb[2][KK], q[KK], qn[KK];
   uint4 vn[VLOADS];
+  // Read through buffer descriptors that end at the last valid row: rows past it read as
+  // zero, with no branch around a load and no register to clear before it.
+  auto tile_rsrc = [](const uint16_t* p, int bytes) {
+    const u32x4 r = buffer_rsrc(p, bytes);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(static_cast<uint64_t>(r[1]) << 32 | r[0]), 0, r[2], r[3]);
+  };
   auto load_tile = [&](int page, int meta, int hr, bf16x8 (&kf)[2][KK]) {
     const int sub = meta >> 8, nv = meta & 255;
     const int64_t slab = (static_cast<int64_t>(page) * a.H + hr / a.R) * a.B * D + static_cast<int64_t>(sub) * kTileKeys * D;
-    const uint16_t* ks = kp + slab;
-    const uint16_t* vs = vp + slab;
+    const auto ks = tile_rsrc(kp + slab, nv * D * 2), vs = tile_rsrc(vp + slab, nv * D * 2);
+    const int at = krow * D * 2 + 16 * half;
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      const int row = 32 * t2 + krow;
+    for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        uint4 raw = make_uint4(0, 0, 0, 0);
-        if (row < nv) raw = *reinterpret_cast<const uint4*>(ks + row * D + 16 * kk + 8 * half);
-        kf[t2][kk] = __builtin_bit_cast(bf16x8, raw);
-      }
-    }
+      for (int kk = 0; kk < KK; ++kk)
+        kf[t2][kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ks, at + 32 * kk, 32 * t2 * D * 2, 0));
 #pragma unroll
-    for (int i = 0; i < VLOADS; ++i) {
-      const int row = i * VROWS + lane / CPR;
-      vn[i] = row < nv ? *reinterpret_cast<const uint4*>(vs + row * D + (lane % CPR) * 8) : make_uint4(0, 0, 0, 0);
-    }
+    for (int i = 0; i < VLOADS; ++i)
+      vn[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(vs, lane * 16 + i % 4 * 1024, i / 4 * 4096, 0));
   };
   auto load_q = [&](int hr) {
     const int h = hr / a.R, g0 = (hr % a.R) * a.G, g1 = min(g0 + a.G, a.lq);
-    const int row = g0 + lane % 32;
+    // ends at the last row's last element
+    const auto rows = tile_rsrc(qp + (static_cast<int64_t>(g0) * a.H + h) * D, ((g1 - g0 - 1) * a.H + 1) * D * 2);
+    const int at = lane % 32 * a.H * D * 2 + 16 * half;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      uint4 raw = make_uint4(0, 0, 0, 0);
-      if (row < g1) raw = *reinterpret_cast<const uint4*>(qp + (static_cast<int64_t>(row) * a.H + h) * D + 16 * kk + 8 * half);
-      qn[kk] = __builtin_bit_cast(bf16x8, raw);
-    }
+    for (int kk = 0; kk < KK; ++kk)
+      qn[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rows, at + 32 * kk, 0, 0));
   };
 
   // ---- per-group softmax state

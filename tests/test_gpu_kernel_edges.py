@@ -202,3 +202,24 @@ def test_gated_combine_rows(dev, dtype, d):
         bound += np.abs(want) * (2.0 ** -24 if dtype == torch.float32 else 2.0 ** -8)
         assert (np.abs(full[1][:rows].cpu().float().numpy() - want) <= bound).all()
         assert torch.equal(full[1][rows:], behind)
+
+
+@pytest.mark.parametrize("top_k", [3, 70])
+def test_small_group_lists_past_count(dev, top_k):
+    """The one-wave-per-group walk reads lists ahead of their counts: whatever stands past a
+    count (ids in and out of range) changes nothing, over several groups a wave and lists
+    longer than a wave's 64 entries."""
+    say(f"entries past the count, top_k={top_k}")
+    H, G, R, bpc, n = 3, 2, 1400, 5, 16
+    _, _, _, cache, _ = make(dev, H, 64, 300, 1, 64, n, torch.bfloat16, 9)
+    g = torch.Generator(device=dev).manual_seed(10)
+    q = torch.randn((R * G - 1, H, 64), generator=g, device=dev).to(torch.bfloat16)
+    idx = torch.rand((H, R, n * bpc), generator=g, device=dev).topk(top_k, dim=-1).indices.to(torch.int32)
+    cnt = torch.randint(0, top_k + 1, (H, R), generator=g, device=dev, dtype=torch.int32)
+    past = torch.arange(top_k, device=dev) >= cnt.unsqueeze(-1)
+    want = omnimem_sparse_attn(cache, q, idx.masked_fill(past, -1), cnt, G, 0.125)
+    for junk in (None, 2**31 - 1, -(2**31), n * bpc):
+        lists = idx if junk is None else idx.masked_fill(past, junk)
+        got = omnimem_sparse_attn(cache, q, lists, cnt, G, 0.125)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
