@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
   // ---- registers of the stream: K of two tiles (current, next), V of the next, Q
   bf16x8 ka[2][KK], kb[2][KK], q[KK], qn[KK];
   uint4 vn[VLOADS];
-  // Read through buffer descriptors that end at the last valid row: rows past it read as
+  // Read through buffer descriptors that end at the last valid key: rows past it read as
   // zero, with no branch around a load and no register to clear before it.
   auto tile_rsrc = [](const uint16_t* p, int bytes) {
     const u32x4 r = buffer_rsrc(p, bytes);
@@ -305,12 +305,10 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
   };
   auto load_q = [&](int hr) {
     const int h = hr / a.R, g0 = (hr % a.R) * a.G, g1 = min(g0 + a.G, a.lq);
-    // ends at the last row's last element
-    const auto rows = tile_rsrc(qp + (static_cast<int64_t>(g0) * a.H + h) * D, ((g1 - g0 - 1) * a.H + 1) * D * 2);
-    const int at = lane % 32 * a.H * D * 2 + 16 * half;
+    // rows past the group's last one repeat it: their results are not stored
+    const uint16_t* row = qp + (static_cast<int64_t>(min(g0 + lane % 32, g1 - 1)) * a.H + h) * D + 8 * half;
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-      qn[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rows, at + 32 * kk, 0, 0));
+    for (int kk = 0; kk < KK; ++kk) qn[kk] = *reinterpret_cast<const bf16x8*>(row + 16 * kk);
   };
 
   // ---- per-group softmax state
