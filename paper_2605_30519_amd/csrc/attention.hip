@@ -14,10 +14,11 @@
 // S^T accumulator registers line up with the B-operand layout of P^T, so P goes from
 // accumulator to MFMA operand with a bf16 pack and nothing else.
 //
-// The same arithmetic runs in two data-movement shapes: k_attn_bf16_r64 (groups of more
-// than 32 rows: 64 rows per wave, tiles by buffer-to-LDS DMA, the keys split over sets of
-// waves where the grid is small) and k_attn_bf16_groups (groups of at most 32 rows: one
-// wave per group, every wave streaming its own groups' tiles).
+// The same formulation runs in three shapes: k_attn_bf16_r64 (d = 128, groups of more than
+// 32 rows: 64 rows per wave) and k_attn_bf16_r32 (d = 64, the same groups: 32 rows per wave),
+// both with tiles by buffer-to-LDS DMA and the keys split over sets of waves where the grid
+// is small; and k_attn_bf16_groups (groups of at most 32 rows: one wave per group, every
+// wave streaming its own groups' tiles).
 //
 // f32 kernel (k_attn_f32): the same formulation on fp32 MFMA, the keys of a 32-row tile
 // split over the waves of its workgroup, for fp32 inputs.
@@ -141,8 +142,8 @@ struct AttnLds {
 // goes from memory straight into registers in the MFMA A-operand layout; V passes
 // through the wave's own LDS tile for the transposing reads.  Lists are read two groups
 // ahead and their pages one, a group's Q rows with its first tile.
-// The arithmetic is that of the 64-row kernel: the same operand layouts, an
-// online softmax, the same rounding.
+// Operand layouts and rounding are those of the kernels for larger groups; the online
+// softmax is the plain one of k_attn_bf16_r32 (the true running max).
 // Bound by the gathers where groups fill the waves (12 heads x 312 groups x 4 blocks:
 // 520 MB at 6.0 TB/s), by one wave's chain of loads and a tile's work where they do not.
 // With a count, list and table read in series before a group's first tile, and each load
@@ -442,8 +443,338 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
   if (cur_hr >= 0) finish(cur_hr);
 }
 
+// max / sum of a value over the lane pair (l, l ^ 32)
+__device__ __forceinline__ float pair_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float pair_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// ------------------------------------------------------------------ bf16 / MFMA, 32 rows per wave
+// d = 64, groups of more than 32 rows: 8 waves, two per SIMD, each own 32 query rows, and the
+// two of a SIMD run a tile half a step apart: waves 0-3 do QK(t), softmax(t), PV(t); waves
+// 4-7 PV(t-1), QK(t), softmax(t), so that one issues MFMAs while the other is in its softmax,
+// which bounds the tile (about 190 VALU operations a wave, 33 of them exponentials, for 16
+// MFMAs).
+// The max of a row is the true one of the tiles so far, so a row's largest P is 1 and its
+// bf16 exact.  A max that lags, as the 64-row kernel's does, rounds the largest P like any
+// other: outputs 2.33e-3 off fp64 against 2.21e-3 (16 heads x 1,560 rows x 4,680 keys).
+// KS key streams: the waves are KS sets of 8 / KS, set j taking tiles j, j + KS, ... of the
+// list; they meet in LDS at the end.  K and V tiles arrive by DMA, a tile ahead, in two
+// stages; where one stream's waves run half a step apart (KS = 1), V has three.
+// 16 heads x 1,560 rows x 64 tiles, two streams: 43.5 us (replayed from a graph), as the
+// 64-row scheme at d = 64 took (43.6); tiles through registers, one stream, 93.2.
+constexpr int kR32Waves = 8;
+
+template <int KS>
+__global__ __launch_bounds__(kR32Waves* kWave) void k_attn_bf16_r32(AttnArgs a) {
+  constexpr int D = 64;
+  using L = KeyTileLds<D>;
+  constexpr int NT = kR32Waves * kWave;
+  constexpr int RW = kR32Waves / KS;  // row waves per stream
+  constexpr int ROWS = RW * 32;
+  constexpr int DT = D / 32;
+  constexpr int KK = D / 16;
+  constexpr int DMA_PER_WAVE = L::TILE / 1024 / RW;
+  constexpr int V_STAGES = KS == 1 ? 3 : 2;
+  constexpr int kKBytes = KS * 2 * L::TILE, kVBytes = KS * V_STAGES * L::TILE;
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[kKBytes + kVBytes];
+  __shared__ __attribute__((aligned(16))) int2 table[2 * NT];
+  __shared__ int scan_tmp[kR32Waves];
+
+  int h, hr, row0, row_end;
+  resolve_tile(a, ROWS, h, hr, row0, row_end);
+  if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
+  const int32_t* list;
+  int count;
+  resolve_list(a, hr, list, count);
+
+  const int tid = threadIdx.x, lane = tid % kWave, half = lane / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wave_r = wave % RW, stream = wave / RW;
+  const bool late = wave >= kR32Waves / 2;
+  // this thread's entry of the first decoded stretch, read without waiting for the count
+  const int id0 = list != nullptr && tid < a.top_k ? list[tid] : INT_MIN;
+  const uint16_t* qp = static_cast<const uint16_t*>(a.q);
+  const float c = a.scale * kLog2e;
+
+  // Q^T as the B operand: lane holds query wrow + lane % 32, d = 16 kk + 8 half + 0..7
+  const int wrow = row0 + wave_r * 32;
+  const bool wave_live = wrow < row_end;  // wave-uniform
+  bf16x8 q[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    q[kk] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+    if (wrow + lane % 32 < row_end)
+      q[kk] = *reinterpret_cast<const bf16x8*>(qp + (static_cast<int64_t>(wrow + lane % 32) * a.H + h) * D + 16 * kk + 8 * half);
+  }
+  f32x16 o[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) o[dt] = f32x16{};
+  float m_run = -INFINITY, l_run = 0.f;  // running max (raw score units), this lane's share of l
+
+  // ---- tile sequence: (page, sub-tile << 8 | valid keys); every stream takes its own of the
+  // next KS entries (an empty tile past the table's end), `more` tells whether there was one
+  // for any of them.  Called by every thread together: it refills the table (with barriers).
+  int next_entry = 0, ntab = 0, ti = 0;
+  bool more = false;
+  auto next_tile = [&]() -> int2 {
+    if (ti >= ntab) {
+      ntab = 0;
+      ti = 0;
+      while (ntab == 0 && next_entry < count) {
+        ntab = decode_tiles<NT>(a, head_table(a, h), list, count, next_entry, table, scan_tmp,
+                                next_entry == 0 ? id0 : INT_MIN);
+        next_entry += NT;
+      }
+      ntab = __builtin_amdgcn_readfirstlane(ntab);
+    }
+    more = ti < ntab;
+    const int2 m = ti + stream < ntab ? table[ti + stream] : make_int2(0, 0);
+    ti += KS;
+    return make_int2(__builtin_amdgcn_readfirstlane(m.x), __builtin_amdgcn_readfirstlane(m.y));
+  };
+
+  // ---- DMA of the wave's share of a tile (instructions wave_r + RW i); an empty tile loads
+  // nothing and writes zeros, rows past the last valid key read as zero
+  const int64_t h_elems = static_cast<int64_t>(__builtin_amdgcn_readfirstlane(h)) * a.B * D;
+  const int64_t page_elems = static_cast<int64_t>(a.H) * a.B * D;
+  const uint16_t* const kp_h = static_cast<const uint16_t*>(a.k_pages) + h_elems;
+  const uint16_t* const vp_h = static_cast<const uint16_t*>(a.v_pages) + h_elems;
+  uint8_t* const k_ring = lds + stream * 2 * L::TILE;
+  uint8_t* const v_ring = lds + kKBytes + stream * V_STAGES * L::TILE;
+  const uint32_t k_dst = lds_offset(k_ring) + wave_r * 1024, v_dst = lds_offset(v_ring) + wave_r * 1024;
+  int k_src[DMA_PER_WAVE], v_src[DMA_PER_WAVE];
+#pragma unroll
+  for (int i = 0; i < DMA_PER_WAVE; ++i) {
+    const int r = L::DMA_ROWS * (wave_r + RW * i) + lane / L::CHUNKS, p = lane % L::CHUNKS;
+    k_src[i] = L::k_pos(r, p);
+    v_src[i] = L::v_pos(r, p);
+  }
+  auto rsrc_of = [&](const uint16_t* base, int2 m) {
+    return buffer_rsrc(base + m.x * page_elems + static_cast<int64_t>(m.y >> 8) * kTileKeys * D, (m.y & 255) * L::ROW);
+  };
+  auto issue_k = [&](int2 m, int st) {
+    const u32x4 r = rsrc_of(kp_h, m);
+#pragma unroll
+    for (int i = 0; i < DMA_PER_WAVE; ++i) dma_16x64(r, k_src[i], k_dst + st * L::TILE + RW * i * 1024);
+  };
+  auto issue_v = [&](int2 m, int st) {
+    const u32x4 r = rsrc_of(vp_h, m);
+#pragma unroll
+    for (int i = 0; i < DMA_PER_WAVE; ++i) dma_16x64(r, v_src[i], v_dst + st * L::TILE + RW * i * 1024);
+  };
+  // this wave's LDS reads have returned and its DMA has landed, and every wave's
+  auto step_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0x70);  // vmcnt 0, lgkmcnt 0
+    lds_barrier();
+  };
+
+  const int krow = s_row_perm(lane % 32);
+  const int v_key = 8 * half + (lane % 16) / 4, v_chunk = 2 * ((lane / 16) % 2) + (lane % 4) / 2;
+  bf16x8 pb[4];
+  auto pv = [&](int st) {
+    typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        uint8_t* p = v_ring + st * L::TILE + L::v_pos(v_key, 4 * dt + v_chunk) + 8 * (lane % 2) + 16 * j * L::ROW;
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)p);
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 4 * L::ROW));
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pb[j], o[dt], 0, 0, 0);
+      }
+  };
+  // scores and softmax of the tile whose K is in stage st
+  auto scores = [&](int st, int nvalid) {
+    f32x16 s[2];
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const bf16x8 k = *reinterpret_cast<const bf16x8*>(k_ring + st * L::TILE + L::k_pos(krow, 2 * kk + half) + 32 * t2 * L::ROW);
+        s[t2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q[kk], kk ? s[t2] : f32x16{}, 0, 0, 0);
+      }
+    if (__builtin_expect(nvalid < kTileKeys, 0)) {  // partial tile: mask the keys past the block's end
+      int kb = 8 * half;
+      asm volatile("" : "+v"(kb));  // a branch, not 32 selects in every tile
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int key = 32 * t2 + (i < 8 ? kb + i : 16 + kb + (i - 8));
+          if (key >= nvalid) s[t2][i] = -INFINITY;
+        }
+    }
+    float m0 = fmaxf(s[0][0], s[1][0]), m1 = fmaxf(s[0][1], s[1][1]);
+#pragma unroll
+    for (int i = 2; i < 16; i += 2) {
+      m0 = fmaxf(m0, fmaxf(s[0][i], s[1][i]));
+      m1 = fmaxf(m1, fmaxf(s[0][i + 1], s[1][i + 1]));
+    }
+    // rescaled in every tile: some of 32 rows' max grows in most, and a branch around the
+    // products costs as many register copies
+    const float m_new = fmaxf(m_run, pair_max(fmaxf(m0, m1)));
+    const float base = m_new == -INFINITY ? 0.f : m_new, mc = base * c;
+    const float alpha = __builtin_amdgcn_exp2f((m_run - base) * c);
+    m_run = m_new;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[dt][i] *= alpha;
+    float sum[2] = {0.f, 0.f};
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(s[t2][i], c, -mc));
+        sum[i % 2] += p;
+        pb[2 * t2 + i / 8][i % 8] = static_cast<__bf16>(p);
+      }
+    l_run = fmaf(l_run, alpha, sum[0] + sum[1]);
+  };
+
+  // ---- Step t uses K(t) and V(t) (late waves V(t-1)) while K(t+1) and V(t+1) arrive; a
+  // stream of late waves takes V a step later, so that two stages hold it.  "V(-1)" is an
+  // empty tile's zeros, and P is zero before the first tile.
+  const bool v_later = KS > 1 && late;
+  int2 cur = next_tile();
+  bool cur_more = more;
+  issue_v(make_int2(0, 0), V_STAGES - 1);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) pb[j] = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0));
+  if (cur_more) {
+    issue_k(cur, 0);
+    if (!v_later) issue_v(cur, 0);
+  }
+  step_barrier();
+  // One loop for each kind of wave (all of them meet at the same barriers): a branch around
+  // the products inside the loop would copy their accumulators.
+  auto walk = [&](auto live_, auto late_) {
+    constexpr bool LIVE = decltype(live_)::value, LATE = decltype(late_)::value;
+    int vst = 0, vprev = V_STAGES - 1;  // V(t)'s stage, V(t-1)'s
+    for (int t = 0; cur_more; ++t) {
+      const int2 nxt = next_tile();
+      const bool nxt_more = more;
+      const int vnext = vst + 1 == V_STAGES ? 0 : vst + 1;
+      if (nxt_more) issue_k(nxt, (t + 1) % 2);
+      if (v_later)
+        issue_v(cur, vst);
+      else if (nxt_more)
+        issue_v(nxt, vnext);
+      if constexpr (LIVE) {
+        if constexpr (LATE) pv(vprev);
+        scores(t % 2, cur.y & 255);
+        if constexpr (!LATE) pv(vst);
+      }
+      step_barrier();
+      vprev = vst;
+      vst = vnext;
+      cur = nxt;
+      cur_more = nxt_more;
+    }
+    if constexpr (LIVE && LATE) pv(vprev);  // the last tile's
+  };
+  if (!wave_live)
+    walk(std::false_type{}, std::false_type{});
+  else if (late)
+    walk(std::true_type{}, std::true_type{});
+  else
+    walk(std::true_type{}, std::false_type{});
+  step_barrier();  // the rings are reused below
+
+  // ---- epilogue: the streams' partial results meet in LDS, rows go through a stage of LDS to
+  // 16-byte nontemporal stores
+  uint16_t* op = static_cast<uint16_t*>(a.out);
+  const float l_tot = pair_sum(l_run);
+  uint8_t* const stage_o = lds + (KS == 1 ? 0 : kKBytes) + wave_r * 32 * L::ROW;
+  static_assert(KS > 1 || ROWS * L::ROW <= kKBytes + kVBytes, "the rings hold the rows");
+  auto stage = [&](int dt, int i4, f32x4 x, float inv) {
+    bf16x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = static_cast<__bf16>(x[e] * inv);
+    *reinterpret_cast<bf16x4*>(stage_o + L::k_pos(lane % 32, 4 * dt + i4) + 8 * half) = w;
+  };
+  float m_all = m_run, l_all = l_tot;
+  if constexpr (KS == 1) {
+    const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        stage(dt, i4, f32x4{o[dt][4 * i4], o[dt][4 * i4 + 1], o[dt][4 * i4 + 2], o[dt][4 * i4 + 3]}, inv);
+  } else {
+    // a unit is 8 of a lane's 32 values of O (dt, pair of i4); stream j owns units
+    // [4 j / KS, 4 (j + 1) / KS), the others hand it theirs, scaled to the rows' common max
+    constexpr int OWN = 4 / KS, SLOTS = KS == 2 ? 2 : 4;  // units per owner, slots per wave
+    static_assert(kR32Waves * SLOTS * 2048 <= kKBytes && RW * 32 * L::ROW <= kVBytes, "the rings hold the exchange and the rows");
+    float* const m_of = reinterpret_cast<float*>(table);  // [wave][32 rows]
+    float* const l_of = m_of + kR32Waves * 32;
+    if (half == 0) {
+      m_of[wave * 32 + lane] = m_run;
+      l_of[wave * 32 + lane] = l_tot;
+    }
+    __syncthreads();
+    float m[KS];
+#pragma unroll
+    for (int j = 0; j < KS; ++j) {
+      m[j] = m_of[(j * RW + wave_r) * 32 + lane % 32];
+      m_all = fmaxf(m_all, m[j]);
+    }
+    l_all = 0.f;
+    auto weight = [&](float mj) { return mj == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mj - m_all) * c); };
+#pragma unroll
+    for (int j = 0; j < KS; ++j) l_all = fmaf(weight(m[j]), l_of[(j * RW + wave_r) * 32 + lane % 32], l_all);
+    const float w = weight(m_run);
+    auto slot = [&](int of_wave, int u, int x) {  // 16 bytes a lane: half x of wave of_wave's unit u
+      return reinterpret_cast<f32x4*>(lds) + ((of_wave * SLOTS + u % SLOTS) * 2 + x) * kWave + lane;
+    };
+    auto mine = [&](int u, int x) {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = o[u / 2][8 * (u % 2) + 4 * x + e] * w;
+      return v;
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (wave_live && u / OWN != stream) {  // wave-uniform
+#pragma unroll
+        for (int x = 0; x < 2; ++x) *slot(wave, u, x) = mine(u, x);
+      }
+    __syncthreads();
+    const float inv = l_all > 0.f ? 1.0f / l_all : 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (wave_live && u / OWN == stream) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          f32x4 v = mine(u, x);
+#pragma unroll
+          for (int j = 1; j < KS; ++j) v += *slot(((stream + j) % KS) * RW + wave_r, u, x);
+          stage(u / 2, 2 * (u % 2) + x, v, inv);
+        }
+      }
+  }
+  __syncthreads();
+  const int row = wrow + lane % 32;
+  if (a.lse && stream == 0 && lane < 32 && row < row_end)
+    a.lse[static_cast<int64_t>(h) * a.lq + row] = l_all > 0.f ? (m_all * c + __log2f(l_all)) * kLn2 : -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 32 * L::CHUNKS / kWave / KS; ++i) {
+    const int cid = stream * kWave + lane + i * KS * kWave;
+    const int r = cid / L::CHUNKS, ch = cid % L::CHUNKS;
+    if (wrow + r < row_end)
+      __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage_o + L::k_pos(r, ch)),
+                                  reinterpret_cast<u32x4*>(op + (static_cast<int64_t>(wrow + r) * a.H + h) * D + ch * 8));
+  }
+}
+
 // ------------------------------------------------------------------ bf16 / MFMA, 64 rows per wave
-// Four waves (one per SIMD) x 64 query rows, as two 32-row halves that share every
+// d = 128.  Four waves (one per SIMD) x 64 query rows, as two 32-row halves that share every
 // K and V operand read from LDS: each 1 KB operand fragment feeds two MFMAs, half the
 // LDS bytes per flop of 32 rows per wave, whose operand traffic equals the LDS
 // bandwidth at the MFMA peak.  With one wave per SIMD the matrix core is kept busy
@@ -457,16 +788,6 @@ __global__ __launch_bounds__(kGrpWaves* kWave, 1) void k_attn_bf16_groups(AttnAr
 constexpr int kR64Waves = 4;
 constexpr float kSlackSum = 256.0f;  // 2^8: how far exponentials may exceed 1 before O is rescaled
 constexpr float kNoMax = -1.0e30f;   // running max before the first tile: finite, below any score
-
-// max / sum of a value over the lane pair (l, l ^ 32)
-__device__ __forceinline__ float pair_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float pair_sum(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 // Pins values at this point of the instruction stream: the exponentials of one half
 // are computed between the other half's MFMAs, not moved down past the check that
@@ -507,29 +828,18 @@ __device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16
                : "+a"(acc), "=&v"(t)
                : "v"(v), "v"(p), "v"(s), "v"(c), "v"(m));
 }
-__device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16x8& p, float& t0, float s0, float m0,
-                                        float& t1, float s1, float m1, float c) {
-  asm volatile(
-      "v_fma_f32 %1, %5, %9, -%6\n\tv_fma_f32 %2, %7, %9, -%8\n\tv_mfma_f32_32x32x16_bf16 %0, %3, %4, %0"
-      : "+a"(acc), "=&v"(t0), "=&v"(t1)
-      : "v"(v), "v"(p), "v"(s0), "v"(m0), "v"(s1), "v"(m1), "v"(c));
-}
 // Sixteen wait states (more than an 8-pass MFMA result needs) before VALU code reads
 // or writes the accumulators; they pass through the asm so that no access moves
 // ahead of it.
 __device__ __forceinline__ void acc_settled(f32x16 (&o)[4]) {
   asm volatile("s_nop 7\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
 }
-__device__ __forceinline__ void acc_settled(f32x16 (&o)[2]) {
-  asm volatile("s_nop 7\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]));
-}
-
-
 // KS key streams: the workgroup's waves are KS sets of 4 / KS row waves, set j walking
 // tiles j, j + KS, ... of the list and the sets meeting in LDS at the end, for grids that
 // would leave CUs idle with 256 rows per workgroup.
-template <int D, int KS>
+template <int KS>
 __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs a) {
+  constexpr int D = 128;
   using L = KeyTileLds<D>;
   constexpr int NT = kR64Waves * kWave;
   constexpr int RW = kR64Waves / KS;  // row waves per stream
@@ -537,12 +847,12 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   constexpr int DT = D / 32;
   constexpr int KK = D / 16;
   constexpr int DMA_PER_WAVE = L::TILE / 1024 / RW;  // 1 KB DMA instructions per wave and tile, K and V each
-  // Four stages of K and V per stream where 128 KB hold them, tile t in stage t mod 4:
+  // Four stages of K and V for one stream (128 KB), tile t in stage t mod 4:
   // iteration t reads the K of tile t and the V of tile t - 1 while tile t + 1 has landed
   // and tile t + 2 arrives in the stage of tile t - 2.
-  // Else two: iteration t reads the K of tile t and the V of tile t - 1 while the K of
+  // Two a stream for two streams: iteration t reads the K of tile t and the V of tile t - 1 while the K of
   // tile t + 1 and the V of tile t arrive in the stages that iteration t - 1 has read.
-  constexpr bool kDeep = KS * 4 * 2 * L::TILE <= 131072;
+  constexpr bool kDeep = KS == 1;
   constexpr int kStages = kDeep ? 4 : 2;
   constexpr int kRing = KS * kStages * L::TILE;
   __shared__ __attribute__((aligned(1024))) uint8_t k_ring[kRing];
@@ -820,12 +1130,9 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // reads of the stages that the next iteration's DMA refills.  "Tile -1" is an
   // all-masked dummy (S = -inf, P = 0, its V stage DMA'd from an empty tile: zeros),
   // and the sequence ends with one empty tile whose iteration finishes the last one.
-  // At d = 64 a run is 16 MFMAs, each carrying a slot of both streams: the softmax VALU
-  // work, which does not depend on d, then bounds the tile.
-  constexpr int NRUN = 4 * KK;                          // MFMAs per run (both halves)
-  constexpr bool BOTH = NRUN == 16;                     // a slot of both streams per MFMA
-  constexpr int FIRST = BOTH ? NRUN - 2 : NRUN / 2 - 1; // slots that ride on the PV run
-  constexpr int TAIL = FIRST + (BOTH ? NRUN : NRUN / 2);
+  constexpr int NRUN = 4 * KK;          // MFMAs per run (both halves)
+  constexpr int FIRST = NRUN / 2 - 1;   // slots that ride on the PV run
+  constexpr int TAIL = FIRST + NRUN / 2;
   static_assert(4 * DT == NRUN / 2 && 2 * KK == NRUN / 2, "QK and PV runs of one length");
   constexpr int DMA_EVERY = NRUN / DMA_PER_WAVE, DMA_AT = DMA_EVERY == 8 ? 5 : DMA_EVERY / 2;
   f32x16 sa0[2], sa1[2], sb0[2], sb1[2];
@@ -892,7 +1199,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
 
   // The operands of the PV MFMA issued last, held until it has read them: those of a run's
   // last one until the next iteration's QK run has begun (waiting for it at the run's end
-  // took 1% of a tile, 4% at d = 64).
+  // took 1% of a tile).
   bf16x8 hold_a = __builtin_bit_cast(bf16x8, make_uint4(0, 0, 0, 0)), hold_b = hold_a;
 
   // Iteration t (t mod kStages = T, a compile-time constant, as are the stages) with tile
@@ -923,8 +1230,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         } else {
           sn1[f / KK] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[f], q1[f % KK], f % KK ? sn1[f / KK] : f32x16{}, 0, 0, 0);
         }
-        if (BOTH || i % 2 == 0) soft_slot(so0, ms0, acc0, pb0, tq0, uq0, FIRST + (BOTH ? i : f));
-        if (BOTH || i % 2 == 1) soft_slot(so1, ms1, acc1, pb1, tq1, uq1, FIRST + (BOTH ? i : f));
+        if (i % 2 == 0) soft_slot(so0, ms0, acc0, pb0, tq0, uq0, FIRST + f);
+        if (i % 2 == 1) soft_slot(so1, ms1, acc1, pb1, tq1, uq1, FIRST + f);
         if (i % 2 == 0 && f + 4 < 2 * KK) kf[f + 4] = k_frag(kst, f + 4);
         if (i == 1) asm volatile("" ::"v"(hold_a), "v"(hold_b));  // the previous PV run's last operands
         if (i % DMA_EVERY == DMA_AT) issue_part(t2, k_into, v_tile, v_into, i / DMA_EVERY);
@@ -953,8 +1260,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         ms0 = tile_max(sn0);
         ms1 = tile_max(sn1);
       }
-      // ---- PV run.  Stream slot (g, half) of tile t rides on MFMA 2 g + half + 2 (g + 2 at
-      // d = 64), past the last MFMA that reads the previous tile's P fragment it overwrites.
+      // ---- PV run.  Stream slot (g, half) of tile t rides on MFMA 2 g + half + 2, past the
+      // last MFMA that reads the previous tile's P fragment it overwrites.
       // An MFMA reads its A and B registers over its passes, so each MFMA's operands
       // are held (an empty asm use) until the end of the next slot, when it has
       // finished: the compiler, which does not see these MFMAs, would otherwise give
@@ -964,11 +1271,9 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         const int f = i / 2;
         const bf16x8 op_a = vf[f], op_b = i % 2 ? pb1[f / DT] : pb0[f / DT];
         f32x16& o = i % 2 ? o1[f % DT] : o0[f % DT];
-        const int g = BOTH ? i - 2 : f - 1;  // the slot that rides on this MFMA
+        const int g = f - 1;  // the slot that rides on this MFMA
         if (i < 2)
           pv_mfma(o, op_a, op_b);
-        else if (BOTH)
-          pv_mfma(o, op_a, op_b, tq0[g], sn0[g / 16][g % 16], ms0, tq1[g], sn1[g / 16][g % 16], ms1, c);
         else if (g < 2)
           pv_mfma(o, op_a, op_b, i % 2 ? tq1[g] : tq0[g], (i % 2 ? sn1 : sn0)[g / 16][g % 16], c, i % 2 ? ms1 : ms0);
         else
@@ -976,8 +1281,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
                   i % 2 ? acc1 : acc0, i % 2 ? uq1[g - 2] : uq0[g - 2]);
         if (i % 2 == 0 && f + 3 < 4 * DT) vf[f + 3] = v_frag(vst, f + 3);
         if (i >= 2) {
-          if (BOTH || i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, g, true, !BOTH);
-          if (BOTH || i % 2 == 1) soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, g, true, !BOTH);
+          if (i % 2 == 0) soft_slot(sn0, ms0, acc0, pb0, tq0, uq0, g, true, true);
+          if (i % 2 == 1) soft_slot(sn1, ms1, acc1, pb1, tq1, uq1, g, true, true);
         }
         if (i > 0) asm volatile("" ::"v"(hold_a), "v"(hold_b));
         hold_a = op_a;
@@ -1060,10 +1365,9 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
     // The streams' partial results of a row wave's 64 rows meet in LDS.  A unit is 32 rows
     // (half g) x 32 of d (dt), 16 values a lane; every unit has an owner among the
     // streams, the others hand it theirs, scaled to the rows' common max.
-    constexpr int UNITS = KS == 2 ? DT : 2 * DT;  // slots for units handed over, per wave (4 KB each)
-    static_assert(KS == 2 || DT == 2, "one unit per stream");
+    constexpr int UNITS = DT;  // slots for units handed over, per wave (4 KB each)
+    static_assert(KS == 2, "a half of the rows per stream");
     static_assert(kR64Waves * UNITS * 4096 <= kRing && RW * STAGE <= kRing, "the rings hold the exchange and the output");
-    auto owner = [](int g, int dt) { return KS == 2 ? g : g + 2 * dt; };
     float* const m_of = reinterpret_cast<float*>(table);  // [wave][64 rows]
     float* const l_of = m_of + kR64Waves * 64;
     static_assert(2 * kR64Waves * 64 * sizeof(float) <= sizeof(table), "the table holds the rows' max and sum");
@@ -1087,8 +1391,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         lt[g] = fmaf(__builtin_amdgcn_exp2f(m[j] - mt[g]), l_of[(j * RW + wave_r) * 64 + 32 * g + lane % 32], lt[g]);
       wt[g] = __builtin_amdgcn_exp2f((g ? ms1 : ms0) - mt[g]);
     }
-    auto unit = [&](int w, int g, int dt) {  // where wave w puts unit (g, dt)
-      return reinterpret_cast<f32x4*>(k_ring) + ((w * UNITS + (KS == 2 ? dt : 2 * g + dt)) * 4) * kWave + lane;
+    auto unit = [&](int w, int dt) {  // where wave w puts the unit of the other's half
+      return reinterpret_cast<f32x4*>(k_ring) + ((w * UNITS + dt) * 4) * kWave + lane;
     };
     if (wave_live) {
       acc_settled(o0);
@@ -1097,8 +1401,8 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
       for (int g = 0; g < 2; ++g)
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          if (stream != owner(g, dt)) {  // wave-uniform
-            f32x4* const to = unit(wave, g, dt);
+          if (stream != g) {  // wave-uniform
+            f32x4* const to = unit(wave, dt);
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
               f32x4 x;
@@ -1116,7 +1420,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
         const float inv = lt[g] > 0.f ? 1.0f / lt[g] : 0.f;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          if (stream == owner(g, dt)) {
+          if (stream == g) {
 #pragma unroll
             for (int i4 = 0; i4 < 4; ++i4) {
               f32x4 x;
@@ -1124,7 +1428,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
               for (int e = 0; e < 4; ++e) x[e] = (g ? o1 : o0)[dt][4 * i4 + e] * wt[g];
 #pragma unroll
               for (int j = 1; j < KS; ++j) {  // the other streams' in one order, from the next on
-                const f32x4 y = unit(((stream + j) % KS) * RW + wave_r, g, dt)[i4 * kWave];
+                const f32x4 y = unit(((stream + j) % KS) * RW + wave_r, dt)[i4 * kWave];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] += y[e];
               }
@@ -1413,16 +1717,16 @@ int group_workgroups(int64_t groups) {
   return static_cast<int>(need < n ? need : n);
 }
 
-// Key streams of the 64-row kernel (1, 2, or with d = 64 up to 4) for `groups` (head, group)
+// Key streams (1 or 2, at d = 64 up to 4) for `groups` (head, group)
 // pairs of `rows` rows: a workgroup of KS streams takes 256 / KS rows and 1 / KS of the
 // time, and the CUs run one workgroup at a time, so the time goes as the rounds of
 // workgroups over CUs times (1 / KS + what a workgroup's start and end take, about 5 of
-// the 64 tiles of a usual list).Measured on 256 CUs with
-// one stream (d = 64: the earlier 32-row kernel) and with the streams chosen here:
+// the 64 tiles of a usual list).  Measured on 256 CUs with
+// one stream (d = 64: tiles through registers) and with the streams chosen here:
 // 5 heads x 3 groups x 1,560 rows, 32 blocks of 128, d = 128: 105 workgroups, 104.7 us;
 //   two streams, 195 workgroups, 62.4-64 us;
 // 16 heads x 1,560 rows over 75 blocks of 64, d = 64: 112 workgroups, 108 us; two streams,
-//   208 workgroups, 54.9 us.
+//   208 workgroups, 52 us.
 // 12 heads x 4,680 rows (228 workgroups, or 444 in two rounds) stays with one.
 template <int D>
 int key_streams(int64_t groups, int rows, int cus) {
@@ -1488,13 +1792,13 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
   }
   constexpr int kThreads = kR64Waves * kWave, kRows = kR64Waves * 64;
   if (g.D == 128) {
-    if (key_streams<128>(groups, rows, device_cus()) == 2) return launch(k_attn_bf16_r64<128, 2>, kRows / 2, kThreads);
-    return launch(k_attn_bf16_r64<128, 1>, kRows, kThreads);
+    if (key_streams<128>(groups, rows, device_cus()) == 2) return launch(k_attn_bf16_r64<2>, kRows / 2, kThreads);
+    return launch(k_attn_bf16_r64<1>, kRows, kThreads);
   }
   switch (key_streams<64>(groups, rows, device_cus())) {
-    case 4: return launch(k_attn_bf16_r64<64, 4>, kRows / 4, kThreads);
-    case 2: return launch(k_attn_bf16_r64<64, 2>, kRows / 2, kThreads);
-    default: return launch(k_attn_bf16_r64<64, 1>, kRows, kThreads);
+    case 4: return launch(k_attn_bf16_r32<4>, kRows / 4, kR32Waves * kWave);
+    case 2: return launch(k_attn_bf16_r32<2>, kRows / 2, kR32Waves * kWave);
+    default: return launch(k_attn_bf16_r32<1>, kRows, kR32Waves * kWave);
   }
 }
 

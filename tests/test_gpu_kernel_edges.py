@@ -135,6 +135,37 @@ def test_key_streams(dev, d, H, Lq, G, K, streams):
     check((dout, dlse), ref, torch.bfloat16, "dense")
 
 
+# One key outweighs the rest of every row, in the last of eight tiles, by less than the 2^8
+# that a lagging max would let pass: with the max of the tiles so far its P is 1, exact in
+# bf16, and a row of O is scaled by nothing but its own rounding.
+@pytest.mark.parametrize("H,Lq,streams", [(2, 300, 4), (8, 2100, 2), (2, 32000, 1)])
+def test_d64_largest_weight(dev, H, Lq, streams):
+    say(f"d=64 largest weight H={H} Lq={Lq}: {streams}")
+    d, S, B, scale = 64, 512, 64, 0.125
+    g = torch.Generator().manual_seed(Lq)
+    q = torch.zeros(Lq, H, d)
+    q[..., 0] = 28 + 13 * torch.rand(Lq, H, generator=g)       # the last tile's key at 5 to 7.4 log2 units
+    k = torch.zeros(1, S, H, d)
+    k[..., 0] = -2.0
+    k[:, [5, 70, 150, 250], :, 0] = 0.0                        # the first tiles' max
+    k[:, S - 20, :, 0] = 1.0
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    v = torch.randn(1, S, H, d, generator=g).to(torch.bfloat16)
+    cache = synth.page_layer(k.to(dev), v.to(dev), B, seed=2)
+    out, lse = omnimem_dense_attn(cache, q.to(dev), 0, 1, scale)
+    rng = np.random.default_rng(Lq)
+    hs, qs = rng.integers(0, H, 500).astype(np.int32), rng.integers(0, Lq, 500).astype(np.int32)
+    ref = oracle.dense_attn(q, k, v, B, 0, 1, scale, hs=hs, qs=qs)
+    check((out, lse), ref, torch.bfloat16, "dense")
+    got, want = out.cpu().float().numpy()[qs, hs].astype(np.float64), ref[0]
+    factor = (got * want).sum(-1) / (want * want).sum(-1) - 1.0
+    rms = float(np.sqrt((factor ** 2).mean()))
+    say(f"  rows scaled by {rms:.2e} rms")
+    # O's rounding, at most 2^-8 and 1.6e-3 rms an element, leaves sqrt(3 / 64) of that in the
+    # projection of 64 normal values (3.5e-4); a rounded largest P adds its own 1.6e-3
+    assert rms <= 8e-4
+
+
 # Probability scores over one, two and three 64-key tiles, exactly full and one key over,
 # in both slice modes; what the compressed cache holds past the history is NaN.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
