@@ -52,7 +52,6 @@ static_assert(kPRows == 128, "the wave layout assumes 128-row slices");
 constexpr int kPKeys = 64;    // pooled keys per tile: 32 per wave, two waves wide
 static_assert(kPKeys == kCmpPageTokens && kPKeys == kTileKeys, "a key tile is one page of the compressed cache");
 constexpr int kPRedStride = kPKeys + 1;
-constexpr float kPNoMax = -1.0e30f;  // running max before the first key: finite, below any score
 constexpr float kLog2eP = 1.4426950408889634f;
 
 template <typename T>
@@ -316,7 +315,7 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   // ---- pass 1: LSE of every row over all pooled keys (S^T = K Q^T, lane = row); s[x][i] is
   // key t*64 + 32 kq + 8 (i/4) + 4 half + i%4 against row 64 rh + 32 x + lane%32; the running
   // max is kept in raw (unscaled) units, scale > 0
-  float m_run[2] = {kPNoMax, kPNoMax}, l_run[2] = {0.f, 0.f}, off[2];
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, off[2];
   auto new_max = [&](const f32x16 (&s)[2]) {
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
@@ -327,9 +326,10 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
         m1 = fmaxf(m1, s[x][i + 1]);
       }
       m0 = fmaxf(m0, m1);
-      l_run[x] *= __builtin_amdgcn_exp2f(c2 * (m_run[x] - m0));
+      const float base = m0 == -INFINITY ? 0.f : m0;  // before the first key every exponential is 0
+      l_run[x] *= __builtin_amdgcn_exp2f(c2 * (m_run[x] - base));
       m_run[x] = m0;
-      off[x] = -c2 * m0;
+      off[x] = -c2 * base;
     }
   };
   auto exponent1 = [&](float s, int i) { return fmaf(s, c2, off[i / 16]); };

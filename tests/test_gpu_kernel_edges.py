@@ -192,6 +192,40 @@ def test_prob_tiles(dev, d, n, G, dtype):
             assert (np.abs(score[h, r, :c] - want) <= 1e-4 * want).all()
 
 
+# Probability scores at the ends of the range: a scale of 1.5e9 over small scores, and scores
+# that are all below -1e36 before a scale of 7e-35; every logit is about +-114, the spread as
+# usual.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d,n,G", [(128, 70, 200), (64, 65, 200), (128, 70, 15)])
+@pytest.mark.parametrize("exp,sign", [(-17, 1.0), (55, -1.0)])
+def test_prob_score_range(dev, exp, sign, d, n, G, dtype):
+    say(f"prob score range 2^{exp} d={d} keys={n} G={G} {dtype}")
+    H, S, B, Lq, K = 2, 64, 64, 200, 5
+    g = torch.Generator().manual_seed(n + d)
+    u = torch.randn(H, d, generator=g)
+    u = 36.0 * (d / 128) ** 0.25 * u / u.norm(dim=-1, keepdim=True)
+    q = ((u + 0.3 * torch.randn(Lq, H, d, generator=g)) * 2.0 ** exp).to(dtype)
+    k = ((sign * u + torch.randn(n, S, H, d, generator=g)) * 2.0 ** exp).to(dtype)
+    scale = d ** -0.5 * 2.0 ** (-2 * exp)
+    if exp > 0:
+        assert float((q[:, 0].double() @ k[:, :, 0].double().flatten(0, 1).t().contiguous()).max()) < -1e36
+    cache = synth.page_layer(k.to(dev), k.to(dev), B, seed=n)
+    cc = CompressedCache.allocate(cache, n)
+    for c in range(n):
+        omnimem_compress_chunk(cache, c, cc)
+    sel = omnimem_select_compressed(cache, cc, q.to(dev), K, G, 0, 0, scale, score_mode=SCORE_PROB)
+    kbar = k.double().mean(dim=1).permute(1, 0, 2).contiguous().numpy()
+    ref = oracle.select_prob(q, kbar, n, 1, K, G, 0, 0, scale, want_all_scores=True)
+    idx, cnt, score = sel.idx.cpu().numpy(), sel.cnt.cpu().numpy(), sel.score.cpu().numpy()
+    check_selection(idx, cnt, ref)
+    want = np.take_along_axis(ref["all_scores"], idx.astype(np.int64), axis=2)
+    # the usual bar, and the pooled keys' two bf16 pieces: 2^-17 of each of the d terms that
+    # make up a logit of 114, at random
+    bar = 1e-4 + 4 * 114 * 2.0 ** -17 * d ** -0.5
+    say(f"  largest relative error {np.abs(score / want - 1).max():.2e}, bar {bar:.2e}")
+    assert (np.abs(score - want) <= bar * want).all()
+
+
 # Mean-logit scores from the pooled keys for one to four groups: 16 (d = 128) or 32 rows per
 # wave, four waves per workgroup; every block selected, so that every score is compared.
 @pytest.mark.parametrize("d,n,G", [(128, 1, 100), (128, 15, 100), (128, 16, 25), (128, 17, 34), (128, 65, 100),
