@@ -315,7 +315,9 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   // ---- pass 1: LSE of every row over all pooled keys (S^T = K Q^T, lane = row); s[x][i] is
   // key t*64 + 32 kq + 8 (i/4) + 4 half + i%4 against row 64 rh + 32 x + lane%32; the running
   // max is kept in raw (unscaled) units, scale > 0
-  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, off[2];
+  // (a tile's exponentials are summed by themselves first: added one by one to a sum over
+  // thousands of keys, each would be rounded to that sum's last bit)
+  float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, sum1[2], off[2];
   auto new_max = [&](const f32x16 (&s)[2]) {
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
@@ -330,6 +332,7 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
       l_run[x] *= __builtin_amdgcn_exp2f(c2 * (m_run[x] - base));
       m_run[x] = m0;
       off[x] = -c2 * base;
+      sum1[x] = 0.f;
     }
   };
   auto exponent1 = [&](float s, int i) { return fmaf(s, c2, off[i / 16]); };
@@ -345,14 +348,18 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   auto add_tile = [&](const f32x16 (&s)[2]) {
     new_max(s);
 #pragma unroll
-    for (int i = 0; i < 34; ++i) slot(s, i, exponent1, l_run);
+    for (int i = 0; i < 34; ++i) slot(s, i, exponent1, sum1);
+    l_run[0] += sum1[0];
+    l_run[1] += sum1[1];
   };
   auto step1 = [&](int t, const f32x16 (&prev)[2], f32x16 (&s)[2]) {
     if constexpr (PIPE) {
       new_max(prev);
-      products(std::true_type{}, t, s, [&](int i) { slot(prev, i, exponent1, l_run); });
-      slot(prev, 32, exponent1, l_run);
-      slot(prev, 33, exponent1, l_run);
+      products(std::true_type{}, t, s, [&](int i) { slot(prev, i, exponent1, sum1); });
+      slot(prev, 32, exponent1, sum1);
+      slot(prev, 33, exponent1, sum1);
+      l_run[0] += sum1[0];
+      l_run[1] += sum1[1];
       mask_tail(t, s);
     } else {
       products(std::true_type{}, t, s, [](int) {});

@@ -6,8 +6,9 @@ import pytest
 import torch
 
 import oracle
-from paper_2605_30519_amd import (SCORE_PROB, CompressedCache, omnimem_compress_chunk, omnimem_dense_attn,
-                                  omnimem_gated_combine, omnimem_select_compressed, omnimem_sparse_attn, synth)
+from paper_2605_30519_amd import (SCORE_PROB, CompressedCache, PagedKVCache, omnimem_compress_chunk,
+                                  omnimem_dense_attn, omnimem_gated_combine, omnimem_select_compressed,
+                                  omnimem_sparse_attn, synth)
 from parity import check_bf16, check_f32, check_lse, check_selection, say
 
 pytestmark = pytest.mark.gpu
@@ -224,6 +225,33 @@ def test_prob_score_range(dev, exp, sign, d, n, G, dtype):
     bar = 1e-4 + 4 * 114 * 2.0 ** -17 * d ** -0.5
     say(f"  largest relative error {np.abs(score / want - 1).max():.2e}, bar {bar:.2e}")
     assert (np.abs(score - want) <= bar * want).all()
+
+
+# A softmax over 16,384 pooled keys that are all alike but for the four largest: exponentials
+# of 0.33 added one by one to a sum of a thousand lose the same part of themselves each time.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("G", [1, 100])
+def test_prob_long_sum(dev, G, dtype):
+    say(f"prob long sum G={G} {dtype}")
+    n, Lq, scale = 16384, 20 * G, 0.125
+    pages = torch.zeros((1, 1, 64, 64), dtype=dtype, device=dev)
+    cache = PagedKVCache(pages, pages, torch.zeros((n, 1), dtype=torch.int32, device=dev), 64)
+    cc = CompressedCache.allocate(cache, n)
+    for t in (cc.k_mean, cc.k_pages, cc.v_pages) + ((cc.k_lo,) if cc.k_lo is not None else ()):
+        t.zero_()
+    top = [0, 4, 32, 36]          # one among the keys of each lane that holds a row
+    cc.k_mean[0, top, 0] = 1.0
+    cc.k_pages[0, 0, top, 0] = 1.0
+    q = torch.zeros(Lq, 1, 64)
+    q[:, 0, 0] = 8.5 + torch.arange(Lq) // G / 8.0     # a group's rows alike
+    sel = omnimem_select_compressed(cache, cc, q.to(dtype).to(dev), 4, G, 0, 0, scale, score_mode=SCORE_PROB)
+    assert (sel.idx.cpu() == torch.tensor(top, dtype=torch.int32)).all()
+    p = 1.0 / (4 + (n - 4) * np.exp(-scale * q[:, 0, 0].double().numpy()))
+    err = np.abs(sel.score.cpu().double().numpy()[0, :, 0] / p.reshape(-1, G).mean(-1) - 1.0).max()
+    say(f"  largest relative error {err:.2e}")
+    # a sum over the 256 tiles: 256 roundings of at most 2^-24, half of that on a growing sum,
+    # and a few more of the exponentials, the log2 of the sum (up to 14) and the exponent
+    assert err <= 1e-5
 
 
 # Mean-logit scores from the pooled keys for one to four groups: 16 (d = 128) or 32 rows per
