@@ -1717,33 +1717,6 @@ int group_workgroups(int64_t groups) {
   return static_cast<int>(need < n ? need : n);
 }
 
-// Key streams (1 or 2, at d = 64 up to 4) for `groups` (head, group)
-// pairs of `rows` rows: a workgroup of KS streams takes 256 / KS rows and 1 / KS of the
-// time, and the CUs run one workgroup at a time, so the time goes as the rounds of
-// workgroups over CUs times (1 / KS + what a workgroup's start and end take, about 5 of
-// the 64 tiles of a usual list).  Measured on 256 CUs with
-// one stream (d = 64: tiles through registers) and with the streams chosen here:
-// 5 heads x 3 groups x 1,560 rows, 32 blocks of 128, d = 128: 105 workgroups, 104.7 us;
-//   two streams, 195 workgroups, 62.4-64 us;
-// 16 heads x 1,560 rows over 75 blocks of 64, d = 64: 112 workgroups, 108 us; two streams,
-//   208 workgroups, 52 us.
-// 12 heads x 4,680 rows (228 workgroups, or 444 in two rounds) stays with one.
-template <int D>
-int key_streams(int64_t groups, int rows, int cus) {
-  int best = 1;
-  double least = 0;
-  for (int ks = 1; ks <= (D == 128 ? 2 : 4); ks *= 2) {
-    const int per_wg = kR64Waves * 64 / ks;
-    const int64_t rounds = (groups * ((rows + per_wg - 1) / per_wg) + cus - 1) / cus;
-    const double time = rounds * (1.0 / ks + 0.08);
-    if (ks == 1 || time < least) {
-      best = ks;
-      least = time;
-    }
-  }
-  return best;
-}
-
 }  // namespace
 
 hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t stream) {
@@ -1791,11 +1764,15 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
     return launch_kernel(k_attn_bf16_groups<64>, dim3(group_workgroups<64>(groups)), threads, 0, stream, a);
   }
   constexpr int kThreads = kR64Waves * kWave, kRows = kR64Waves * 64;
+  static_assert(kRows == kAttnRows && kR32Waves * 32 == kAttnRows, "rows of a workgroup with one key stream");
+  // the longest list that a group may have, in tiles
+  const int64_t blocks = L.idx == nullptr ? L.dense_num_blocks : L.top_k < g.nb ? L.top_k : g.nb;
+  const int streams = attn_key_streams(g.D, groups, rows, blocks * (g.B / kTileKeys), device_cus());
   if (g.D == 128) {
-    if (key_streams<128>(groups, rows, device_cus()) == 2) return launch(k_attn_bf16_r64<2>, kRows / 2, kThreads);
+    if (streams == 2) return launch(k_attn_bf16_r64<2>, kRows / 2, kThreads);
     return launch(k_attn_bf16_r64<1>, kRows, kThreads);
   }
-  switch (key_streams<64>(groups, rows, device_cus())) {
+  switch (streams) {
     case 4: return launch(k_attn_bf16_r32<4>, kRows / 4, kR32Waves * kWave);
     case 2: return launch(k_attn_bf16_r32<2>, kRows / 2, kR32Waves * kWave);
     default: return launch(k_attn_bf16_r32<1>, kRows, kR32Waves * kWave);

@@ -76,6 +76,12 @@ struct AttnLaunch {
   float scale;
 };
 
+// Key streams of the bf16 kernels for groups of more than 32 rows: 1 or 2, at d = 64 up to 4.
+// `groups` (head, group) pairs of `rows` rows, lists of at most `tiles` 64-key tiles, `cus`
+// compute units.
+constexpr int kAttnRows = 256;  // query rows of a workgroup with one stream
+int attn_key_streams(int D, int64_t groups, int rows, int64_t tiles, int cus);
+
 // ---------------------------------------------------------------- union gather
 struct UnionPlan {
   size_t off_flags, off_table, off_kbuf, off_vbuf, total;

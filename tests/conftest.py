@@ -1,4 +1,6 @@
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -26,6 +28,19 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(scope="session")
+def host_shim(tmp_path_factory):
+    """The library's HIP-free host units behind tests/host_shim.cpp, built with g++."""
+    csrc = os.path.join(ROOT, "paper_2605_30519_amd", "csrc")
+    so = str(tmp_path_factory.mktemp("shim") / "host_shim.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(ROOT, "tests", "host_shim.cpp"),
+                    *(os.path.join(csrc, f) for f in ("validate.cpp", "plan.cpp", "lru_core.cpp", "numa.cpp")), "-o", so],
+                   check=True)
+    shim = ctypes.CDLL(so)
+    shim.shim_key_streams.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_int32]
+    return shim
 
 
 @pytest.fixture(scope="session")

@@ -16,6 +16,10 @@ using namespace omnimem;
 
 extern "C" {
 
+int32_t shim_key_streams(int32_t d, int64_t groups, int32_t rows, int64_t tiles, int32_t cus) {
+  return attn_key_streams(d, groups, rows, tiles, cus);
+}
+
 int32_t omnimem_blocks_per_chunk(int32_t s, int32_t b) { return blocks_per_chunk(s, b); }
 int32_t omnimem_awe_active(int32_t n, int32_t e, int32_t t, int32_t k, int32_t bpc) { return awe_active(n, e, t, k, bpc); }
 const char* omnimem_status_string(int32_t st) { return status_string(st); }

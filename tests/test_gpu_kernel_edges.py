@@ -90,20 +90,26 @@ def test_fp32_attention_long(dev, d, n):
     assert np.allclose(lse.cpu().numpy()[hs, qs], l_ref, rtol=2e-6, atol=1e-5)
 
 
-# The 64-row bf16 kernel in each of its key-stream counts (chosen by how many workgroups
-# the grid has): block lists of every length, in any order, with tail blocks of 8 tokens,
-# padding, duplicates, non-resident blocks, scores that jump between blocks far above
-# the running max, lists of more than one decoded stretch (256 entries) and of an odd
-# number of tiles.
+def key_streams(shim, d, H, Lq, G, tiles):
+    """How many key streams a bf16 call with groups of more than 32 rows gets on this GPU."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return shim.shim_key_streams(d, H * -(-Lq // G), min(G, Lq), tiles, cus)
+
+
+# The bf16 kernels of larger groups in each of their key-stream counts: block lists of every
+# length, in any order, with tail blocks of 8 tokens, padding, duplicates, non-resident
+# blocks, scores that jump between blocks far above the running max, lists of more than one
+# decoded stretch (256 entries, at d = 64 512) and of an odd number of tiles.
 @pytest.mark.parametrize("d,H,Lq,G,K,streams", [(128, 2, 300, 130, 25, 2), (128, 2, 33, 33, 601, 2),
                                                 (128, 2, 32000, 250, 25, 1), (128, 2, 32000, 250, 601, 1),
                                                 (64, 2, 300, 130, 25, 4), (64, 3, 65, 65, 601, 4),
                                                 (64, 8, 2100, 2100, 25, 2), (64, 8, 2100, 2100, 601, 2),
                                                 (64, 2, 32000, 250, 25, 1), (64, 2, 32000, 250, 601, 1)])
-def test_key_streams(dev, d, H, Lq, G, K, streams):
+def test_key_streams(dev, host_shim, d, H, Lq, G, K, streams):
     say(f"key streams d={d} H={H} Lq={Lq} G={G} K={K}: {streams}")
     S, B, n = 200, 64, 5
     nb = n * 4
+    assert key_streams(host_shim, d, H, Lq, G, min(K, nb)) == streams == key_streams(host_shim, d, H, Lq, Lq, nb)
     g = torch.Generator().manual_seed(d + K)
     u = torch.randn(H, d, generator=g)
     u = 3.0 * u / u.norm(dim=-1, keepdim=True)
@@ -140,8 +146,9 @@ def test_key_streams(dev, d, H, Lq, G, K, streams):
 # that a lagging max would let pass: with the max of the tiles so far its P is 1, exact in
 # bf16, and a row of O is scaled by nothing but its own rounding.
 @pytest.mark.parametrize("H,Lq,streams", [(2, 300, 4), (8, 2100, 2), (2, 32000, 1)])
-def test_d64_largest_weight(dev, H, Lq, streams):
+def test_d64_largest_weight(dev, host_shim, H, Lq, streams):
     say(f"d=64 largest weight H={H} Lq={Lq}: {streams}")
+    assert key_streams(host_shim, 64, H, Lq, Lq, 8) == streams
     d, S, B, scale = 64, 512, 64, 0.125
     g = torch.Generator().manual_seed(Lq)
     q = torch.zeros(Lq, H, d)
