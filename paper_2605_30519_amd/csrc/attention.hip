@@ -1602,7 +1602,7 @@ __global__ __launch_bounds__(F32Shape<D>::NW* kWave, 2) void k_attn_f32(AttnArgs
       float mx = s0[0];
 #pragma unroll
       for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s0[i]);
-      mx = fmaxf(mx, __shfl_xor(mx, 32)) * a.scale;
+      mx = pair_max(mx) * a.scale;
       if (__any(mx > m_run)) {  // rescale only when some row's running max grows
         const float m_new = fmaxf(m_run, mx);
         const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * kLog2e);
@@ -1635,7 +1635,7 @@ __global__ __launch_bounds__(F32Shape<D>::NW* kWave, 2) void k_attn_f32(AttnArgs
 
   // ---- the waves' partial results meet in LDS: O^T element (dt, i) is d = DT c + dt of
   // c = 8 (i / 4) + 4 half + i % 4
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float l_tot = pair_sum(l_run);
   if (half == 0) {
     m_lds[wave][col] = m_run;
     l_lds[wave][col] = l_tot;

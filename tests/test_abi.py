@@ -328,3 +328,12 @@ def test_scratch_guard_reads_resource_remarks():
     assert bad == [f"{r64}: ScratchSize [bytes/lane]: 1088"]
     bad = _build.scratch_users(remarks(r64, 0, 5), kernels)
     assert bad == [f"{r64}: VGPRs Spill: 5"]
+
+
+def test_scratch_guard_covers_fp32_attention():
+    """The fp32 kernel of d = 128, which uses every register it may, is guarded too."""
+    from paper_2605_30519_amd import _build
+
+    name = "_ZN7omnimem12_GLOBAL__N_110k_attn_f32ILi128EEEvNS0_8AttnArgsE"
+    spilled = f"x: remark: Function Name: {name} [-R]\nx: remark:     VGPRs Spill: 3 [-R]"
+    assert _build.scratch_users(spilled, _build.NO_SCRATCH["attention.hip"]) == [f"{name}: VGPRs Spill: 3"]
