@@ -53,11 +53,11 @@ struct AttnArgs {
   void* out;
   float* lse;
   int tiles_per_group;
+  int first_wg;  // workgroups of the call before this grid
 };
 
-__device__ __forceinline__ void resolve_tile(const AttnArgs& a, int rows_per_wg, int& h, int& hr, int& row0,
+__device__ __forceinline__ void resolve_tile(const AttnArgs& a, int id, int rows_per_wg, int& h, int& hr, int& row0,
                                              int& row_end) {
-  const int id = xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int tile = id % a.tiles_per_group;
   hr = id / a.tiles_per_group;
   const int r = hr % a.R;
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kR32Waves* kWave) void k_attn_bf16_r32(AttnArgs a) 
   __shared__ int scan_tmp[kR32Waves];
 
   int h, hr, row0, row_end;
-  resolve_tile(a, ROWS, h, hr, row0, row_end);
+  resolve_tile(a, xcd_contiguous_id(blockIdx.x, gridDim.x), ROWS, h, hr, row0, row_end);
   if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
   const int32_t* list;
   int count;
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   __shared__ int scan_tmp[kR64Waves];
 
   int h, hr, row0, row_end;
-  resolve_tile(a, ROWS, h, hr, row0, row_end);
+  resolve_tile(a, xcd_contiguous_id(blockIdx.x, gridDim.x), ROWS, h, hr, row0, row_end);
   if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
   const int32_t* list;
   int count;
@@ -1494,7 +1494,7 @@ __global__ __launch_bounds__(F32Shape<D>::NW* kWave, 2) void k_attn_f32(AttnArgs
   __shared__ int scan_tmp[NW];
 
   int h, hr, row0, row_end;
-  resolve_tile(a, kF32Rows, h, hr, row0, row_end);
+  resolve_tile(a, a.first_wg + xcd_contiguous_id(blockIdx.x, gridDim.x), kF32Rows, h, hr, row0, row_end);
   if (row0 >= row_end) return;  // workgroup-uniform: no barrier has been reached
   const int32_t* list;
   int count;
@@ -1743,6 +1743,7 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
   a.scale = L.scale;
   a.out = L.out;
   a.lse = L.lse;
+  a.first_wg = 0;
   const int rows = L.group_size < L.lq ? L.group_size : L.lq;
   const int64_t groups = static_cast<int64_t>(g.H) * L.R;
   if (groups <= 0 || groups > 0x7fffffff) return groups <= 0 ? hipSuccess : hipErrorInvalidConfiguration;
@@ -1752,9 +1753,22 @@ hipError_t launch_attention(const CacheGeom& g, const AttnLaunch& L, hipStream_t
     if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
     return launch_kernel(kernel, dim3(static_cast<unsigned>(nwg)), dim3(threads), 0, stream, a);
   };
+  // A group of one row has a workgroup of its own, and a grid holds fewer than 2^32 threads,
+  // 8.4 M workgroups at d = 64: more of them go in several grids.
+  auto launch_f32 = [&](auto kernel, int threads) {
+    a.tiles_per_group = (rows + kF32Rows - 1) / kF32Rows;
+    const int64_t nwg = groups * a.tiles_per_group, most = 0xffffffffll / threads;
+    if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
+    LaunchStatus st;
+    for (int64_t first = 0; first < nwg; first += most) {
+      a.first_wg = static_cast<int>(first);
+      st(kernel, dim3(static_cast<unsigned>(nwg - first < most ? nwg - first : most)), dim3(threads), 0, stream, a);
+    }
+    return st.err;
+  };
   if (g.dtype != 0) {
-    if (g.D == 128) return launch(k_attn_f32<128>, kF32Rows, F32Shape<128>::NW * kWave);
-    return launch(k_attn_f32<64>, kF32Rows, F32Shape<64>::NW * kWave);
+    if (g.D == 128) return launch_f32(k_attn_f32<128>, F32Shape<128>::NW * kWave);
+    return launch_f32(k_attn_f32<64>, F32Shape<64>::NW * kWave);
   }
   if (rows <= 32) {  // one 32-row tile per group: a wave per group
     a.tiles_per_group = 1;

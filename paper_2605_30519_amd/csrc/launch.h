@@ -16,10 +16,13 @@ namespace omnimem {
 // Launches one kernel and returns that launch's own status.  The runtime's
 // per-thread "last error" is neither read nor cleared, so an error left there by
 // the caller's own HIP work is not reported as the library's, and is not lost.
+// A grid of 2^32 threads or more is refused here: the runtime takes it without an error
+// and runs a part of it.
 template <typename... KArgs, typename... Args>
 inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t shmem, hipStream_t stream,
                                 Args&&... args) {
   static_assert(sizeof...(KArgs) == sizeof...(Args), "kernel argument count");
+  if (static_cast<uint64_t>(grid.x) * block.x > 0xffffffffu) return hipErrorInvalidConfiguration;
   std::tuple<std::decay_t<KArgs>...> vals(static_cast<std::decay_t<KArgs>>(std::forward<Args>(args))...);
   void* ptrs[sizeof...(KArgs) > 0 ? sizeof...(KArgs) : 1] = {};
   std::apply([&ptrs](auto&... v) {

@@ -90,6 +90,28 @@ def test_fp32_attention_long(dev, d, n):
     assert np.allclose(lse.cpu().numpy()[hs, qs], l_ref, rtol=2e-6, atol=1e-5)
 
 
+def test_fp32_more_groups_than_a_grid(dev):
+    """Groups of one row are a workgroup each, 512 threads at d = 64, and a grid holds fewer
+    than 2^32 threads (of more, a part runs): 70 groups more than one grid."""
+    most = (2 ** 32 - 1) // 512
+    Lq, n, scale = most + 70, 5, 0.125
+    say(f"fp32 attention, {Lq} groups of one row")
+    g = torch.Generator(device=dev).manual_seed(3)
+    k, v = (torch.randn((n, 1, 64, 64), generator=g, device=dev) for _ in range(2))
+    cache = PagedKVCache(k, v, torch.arange(n, dtype=torch.int32, device=dev).view(n, 1), 64)
+    q = torch.randn((Lq, 1, 64), generator=g, device=dev)
+    idx = torch.randint(0, n, (1, Lq, 1), generator=g, device=dev, dtype=torch.int32)
+    out, lse = omnimem_sparse_attn(cache, q, idx, torch.ones((1, Lq), dtype=torch.int32, device=dev), 1, scale)
+    torch.cuda.synchronize()
+    rows = torch.cat([torch.arange(300), most - 200 + torch.arange(270),
+                      torch.randint(0, Lq, (2000,), generator=torch.Generator().manual_seed(4))]).to(dev)
+    block = idx[0, rows, 0].long()
+    u = scale * (k[block, 0].double() * q[rows].double()).sum(-1)
+    want = (torch.softmax(u, -1).unsqueeze(-1) * v[block, 0].double()).sum(1)
+    check_f32(out[rows, 0].cpu().numpy(), want.cpu().numpy(), "sparse")
+    check_lse(lse[0, rows].cpu().numpy(), torch.logsumexp(u, -1).cpu().numpy(), "lse", 1e-5)
+
+
 def key_streams(shim, d, H, Lq, G, tiles):
     """How many key streams a bf16 call with groups of more than 32 rows gets on this GPU."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
