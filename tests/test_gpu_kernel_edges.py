@@ -121,24 +121,27 @@ def key_streams(shim, d, H, Lq, G, tiles):
 # The bf16 kernels of larger groups in each of their key-stream counts: block lists of every
 # length, in any order, with tail blocks of 8 tokens, padding, duplicates, non-resident
 # blocks, scores that jump between blocks far above the running max, lists of more than one
-# decoded stretch (256 entries, at d = 64 512) and of an odd number of tiles.
+# decoded stretch (256 entries, at d = 64 512) and of an odd number of tiles.  Blocks of 128
+# tokens are two tiles, each with a jump of its own, the second of a tail block 8 tokens.
+@pytest.mark.parametrize("B", [64, 128])
 @pytest.mark.parametrize("d,H,Lq,G,K,streams", [(128, 2, 300, 130, 25, 2), (128, 2, 33, 33, 601, 2),
                                                 (128, 2, 32000, 250, 25, 1), (128, 2, 32000, 250, 601, 1),
                                                 (64, 2, 300, 130, 25, 4), (64, 3, 65, 65, 601, 4),
                                                 (64, 8, 2100, 2100, 25, 2), (64, 8, 2100, 2100, 601, 2),
                                                 (64, 2, 32000, 250, 25, 1), (64, 2, 32000, 250, 601, 1)])
-def test_key_streams(dev, host_shim, d, H, Lq, G, K, streams):
-    say(f"key streams d={d} H={H} Lq={Lq} G={G} K={K}: {streams}")
-    S, B, n = 200, 64, 5
-    nb = n * 4
-    assert key_streams(host_shim, d, H, Lq, G, min(K, nb)) == streams == key_streams(host_shim, d, H, Lq, Lq, nb)
+def test_key_streams(dev, host_shim, d, H, Lq, G, K, streams, B):
+    say(f"key streams d={d} H={H} Lq={Lq} G={G} K={K} B={B}: {streams}")
+    S, n = 200, 5
+    nb = n * -(-S // B)
+    tiles = min(K, nb) * B // 64
+    assert key_streams(host_shim, d, H, Lq, G, tiles) == streams == key_streams(host_shim, d, H, Lq, Lq, nb * B // 64)
     g = torch.Generator().manual_seed(d + K)
     u = torch.randn(H, d, generator=g)
     u = 3.0 * u / u.norm(dim=-1, keepdim=True)
     q = (u + 0.3 * torch.randn(Lq, H, d, generator=g)).to(torch.bfloat16)
     jump = torch.tensor([1.0, 40.0, 1.0, 0.5, 400.0, 2.0, 0.25, 60.0, 1.0, 3.0, 400.0, 1.0, 0.1, 8.0, 1.0, 50.0, 1.0, 0.3,
                          20.0, 1.0])
-    tokens = torch.arange(S) // B
+    tokens = torch.arange(S) // 64
     k = (u + 0.3 * torch.randn(n, S, H, d, generator=g)) * jump.view(n, 4)[:, tokens].view(n, S, 1, 1)
     k = k.to(torch.bfloat16)
     v = torch.randn(n, S, H, d, generator=g).to(torch.bfloat16)
@@ -162,6 +165,44 @@ def test_key_streams(dev, host_shim, d, H, Lq, G, K, streams):
     check((out, lse), ref, torch.bfloat16, "sparse")
     ref = oracle.dense_attn(q, k, v, B, 0, n, scale, resident=resident, hs=hs, qs=qs)
     check((dout, dlse), ref, torch.bfloat16, "dense")
+
+
+# Block lists by rising and by falling scores, the highest in a full block or in a tail block
+# (of 128 tokens: in its second tile, 64 or 8 keys), and one that starts with a tail block:
+# with rising scores every tile but a stream's first must settle against a max of earlier
+# tiles, and the last one decides the result.
+@pytest.mark.parametrize("B", [64, 128])
+@pytest.mark.parametrize("d,H,Lq,G,streams", [(128, 2, 32000, 250, 1), (128, 2, 300, 300, 2), (64, 2, 32000, 250, 1),
+                                              (64, 8, 2100, 2100, 2), (64, 2, 300, 300, 4)])
+def test_ordered_jumps(dev, host_shim, d, H, Lq, G, streams, B):
+    S, n = 200, 5
+    bpc = -(-S // B)
+    nb, R, scale = n * bpc, -(-Lq // G), d ** -0.5
+    assert key_streams(host_shim, d, H, Lq, G, nb * B // 64) == streams
+    g = torch.Generator().manual_seed(d + B)
+    u = torch.randn(H, d, generator=g)
+    u = 3.0 * u / u.norm(dim=-1, keepdim=True)
+    q = (u + 0.3 * torch.randn(Lq, H, d, generator=g)).to(torch.bfloat16)
+    qd = q.to(dev)
+    v = torch.randn(n, S, H, d, generator=g).to(torch.bfloat16)
+    rng = np.random.default_rng(B)
+    hs, qs = rng.integers(0, H, 300).astype(np.int32), rng.integers(0, Lq, 300).astype(np.int32)
+    for where, top in (("full", 2 * bpc), ("tail", 3 * bpc - 1)):
+        jump = torch.tensor([1.0, 40.0, 1.5, 0.5, 30.0, 2.0, 0.25, 60.0, 1.2, 3.0, 30.0, 0.7, 0.1, 8.0, 1.1, 50.0, 0.9, 0.3,
+                             20.0, 5.0]).view(nb, B // 64).sort(dim=-1).values      # a factor for each tile
+        jump[top] *= 400.0 / jump[top].max()
+        k = (u + 0.3 * torch.randn(n, S, H, d, generator=g)) * jump.view(n, -1)[:, torch.arange(S) // 64].view(n, S, 1, 1)
+        k = k.to(torch.bfloat16)
+        cache = synth.page_layer(k.to(dev), v.to(dev), B, seed=B, pad_value=NAN)
+        up = torch.argsort(jump[:, -1])
+        first = torch.tensor([bpc - 1])
+        for name, ids in (("rising", up), ("falling", up.flip(0)), ("tail first", torch.cat([first, up[up != bpc - 1]]))):
+            say(f"ordered jumps d={d} H={H} Lq={Lq} G={G} B={B}: {streams}, top in a {where} block, {name}")
+            idx = ids.to(torch.int32).view(1, 1, nb).expand(H, R, nb).contiguous()
+            cnt = torch.full((H, R), nb, dtype=torch.int32)
+            got = omnimem_sparse_attn(cache, qd, idx.to(dev), cnt.to(dev), G, scale)
+            ref = oracle.sparse_attn(q, k, v, B, idx.numpy(), cnt.numpy(), G, scale, hs=hs, qs=qs)
+            check(got, ref, torch.bfloat16, name)
 
 
 # One key outweighs the rest of every row, in the last of eight tiles, by less than the 2^8
