@@ -834,6 +834,7 @@ __device__ __forceinline__ void pv_mfma(f32x16& acc, const bf16x8& v, const bf16
 __device__ __forceinline__ void acc_settled(f32x16 (&o)[4]) {
   asm volatile("s_nop 7\n\ts_nop 7" : "+a"(o[0]), "+a"(o[1]), "+a"(o[2]), "+a"(o[3]));
 }
+
 // KS key streams: the workgroup's waves are KS sets of 4 / KS row waves, set j walking
 // tiles j, j + KS, ... of the list and the sets meeting in LDS at the end, for grids that
 // would leave CUs idle with 256 rows per workgroup.
@@ -850,8 +851,9 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
   // Four stages of K and V for one stream (128 KB), tile t in stage t mod 4:
   // iteration t reads the K of tile t and the V of tile t - 1 while tile t + 1 has landed
   // and tile t + 2 arrives in the stage of tile t - 2.
-  // Two a stream for two streams: iteration t reads the K of tile t and the V of tile t - 1 while the K of
-  // tile t + 1 and the V of tile t arrive in the stages that iteration t - 1 has read.
+  // Two a stream for two streams: iteration t reads the K of tile t and the V of tile t - 1
+  // while the K of tile t + 1 and the V of tile t arrive in the stages that iteration t - 1
+  // has read.
   constexpr bool kDeep = KS == 1;
   constexpr int kStages = kDeep ? 4 : 2;
   constexpr int kRing = KS * kStages * L::TILE;

@@ -20,7 +20,6 @@ template <>
 struct Chunk<uint16_t> {
   static constexpr int N = 8;
   __device__ __forceinline__ static void store(uint16_t* p, const float (&x)[8]) {
-    typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
     bf16x8 w;  // nearest even, two a conversion
 #pragma unroll
     for (int j = 0; j < 8; ++j) w[j] = static_cast<__bf16>(x[j]);

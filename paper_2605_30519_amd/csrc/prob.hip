@@ -74,7 +74,6 @@ struct ProbArgs {
   int64_t tile_stride, head_stride;
   int ntiles, nb;
   float scale;
-  int multi;            // 1: a slice holds gps whole groups; 0: a slice is part of one group
   int gps, spg, slices, nseg;
   float* part;          // [H][nseg][nb] (parts of groups)
   // whole-group slices write the ranking keys themselves
@@ -571,7 +570,6 @@ hipError_t launch_prob_typed(const CacheGeom& g, const SelectPlan& p, const void
   a.ntiles = ntiles;
   a.nb = g.nb;
   a.scale = p.scale;
-  a.multi = p.prob_multi ? 1 : 0;
   a.gps = p.prob_gps;
   a.spg = p.prob_spg;
   a.slices = p.prob_slices;
@@ -583,11 +581,11 @@ hipError_t launch_prob_typed(const CacheGeom& g, const SelectPlan& p, const void
   a.page_table = g.page_table;
   a.pt_stride = g.pt_stride;
   a.num_pages = g.num_pages;
-  if (a.multi)
+  if (p.prob_multi)
     st(k_prob_partial<T, D, true>, dim3(p.prob_slices * g.H), dim3(kPThreads), 0, stream, a);
   else
     st(k_prob_partial<T, D, false>, dim3(p.prob_slices * g.H), dim3(kPThreads), 0, stream, a);
-  if (!a.multi) {
+  if (!p.prob_multi) {
     constexpr int kMergeKeys = kPThreads / kMergeLanes;
     const dim3 mgrid((g.nb + kMergeKeys - 1) / kMergeKeys, p.R, g.H);
     st(k_prob_merge, mgrid, dim3(kPThreads), 0, stream, part, p.prob_nseg, g.nb, nbp, p.lq, p.G, p.R, p.prob_spg,
