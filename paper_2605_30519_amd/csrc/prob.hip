@@ -145,31 +145,41 @@ __global__ __launch_bounds__(kPThreads) void k_split_keys(const float* __restric
 // Split-key tiles through registers (the second pass over slices of whole groups): 16-byte
 // chunk e of tile t (piece e / (64 CH), key row, chunk c) is fetched by thread e mod 256.
 template <int D>
-__device__ __forceinline__ void fetch_tile(const ProbArgs& a, int h, int t, u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads]) {
+__device__ __forceinline__ void fetch_tile(const ProbArgs& a, int h, int t, int tid,
+                                           u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads]) {
   constexpr int PIECE_CHUNKS = kPKeys * D / 8;
   static_assert(PIECE_CHUNKS % kPThreads == 0, "a thread's chunks of a tile lie in one piece each");
   const int64_t off = t * a.tile_stride + h * a.head_stride;
 #pragma unroll
   for (int u = 0; u < 2 * PIECE_CHUNKS / kPThreads; ++u) {
-    const int e = threadIdx.x + u * kPThreads, piece = e / PIECE_CHUNKS;  // piece: compile-time per u
-    kv[u] = reinterpret_cast<const u32x4*>(a.piece[piece])[off + e % PIECE_CHUNKS];
+    constexpr int N = PIECE_CHUNKS / kPThreads;  // loads a piece
+    kv[u] = reinterpret_cast<const u32x4*>(a.piece[u / N])[off + u % N * kPThreads + tid];
   }
 }
 
 template <int D>
-__device__ __forceinline__ void stage_tile(const u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads], uint8_t* ktile) {
-  constexpr int CH = D / 8;
+__device__ __forceinline__ void stage_tile(const u32x4 (&kv)[2 * kPKeys * D / 8 / kPThreads], uint8_t* ktile, int tid) {
+  constexpr int CH = D / 8, N = kPKeys * CH / kPThreads;
 #pragma unroll
-  for (int u = 0; u < 2 * kPKeys * CH / kPThreads; ++u) {
-    const int e = threadIdx.x + u * kPThreads, piece = e / (kPKeys * CH), rem = e % (kPKeys * CH);
-    *reinterpret_cast<u32x4*>(ktile + piece * KeyTileLds<D>::TILE + KeyTileLds<D>::k_pos(rem / CH, rem % CH)) = kv[u];
+  for (int u = 0; u < 2 * N; ++u) {
+    const int e = u % N * kPThreads + tid;
+    *reinterpret_cast<u32x4*>(ktile + u / N * KeyTileLds<D>::TILE + KeyTileLds<D>::k_pos(e / CH, e % CH)) = kv[u];
   }
+}
+
+// Workgroups that a CU holds, by registers and LDS.  Three at d = 64 for bf16 queries: 170
+// registers instead of 168 in the whole-group form left two, 16 heads x 74 groups of 64 rows
+// x 4,440 keys in 619 us (the whole selection) instead of 412.
+template <typename T, int D>
+constexpr int prob_per_cu() {
+  return D == 64 && QueryPieces<T>::N == 1 ? 3 : 2;
 }
 
 // MULTI: the slice holds whole groups, and a 128 x 64 probability tile is reduced
 // through LDS in the second pass.
 template <typename T, int D, bool MULTI>
-__global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
+__global__ __launch_bounds__(kPThreads, (prob_per_cu<T, D>())) void k_prob_partial(ProbArgs a) {
+  constexpr int kPerCu = prob_per_cu<T, D>();
   using L = KeyTileLds<D>;
   constexpr int KK = D / 16;                      // MFMA steps over d
   constexpr int CH = D / 8;                       // 16-byte chunks per key row
@@ -460,12 +470,16 @@ __global__ __launch_bounds__(kPThreads, 2) void k_prob_partial(ProbArgs a) {
   } else {
     const int ngroups = min(a.gps, a.R - seg0);
     u32x4 kv[LPT];
-    fetch_tile<D>(a, h, 0, kv);
+    // at d = 64 the tile's addresses are formed here, not held in registers through the first
+    // pass, which leaves 168 a lane for three workgroups on a CU
+    int tid2 = tid;
+    if constexpr (kPerCu == 3) asm volatile("" : "+v"(tid2));
+    fetch_tile<D>(a, h, 0, tid2, kv);
     for (int t = 0; t < a.ntiles; ++t) {
       __syncthreads();
-      stage_tile<D>(kv, lds);
+      stage_tile<D>(kv, lds, tid2);
       __syncthreads();
-      if (t + 1 < a.ntiles) fetch_tile<D>(a, h, t + 1, kv);
+      if (t + 1 < a.ntiles) fetch_tile<D>(a, h, t + 1, tid2, kv);
       f32x16 acc[2] = {};
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) {

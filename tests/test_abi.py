@@ -330,10 +330,13 @@ def test_scratch_guard_reads_resource_remarks():
     assert bad == [f"{r64}: VGPRs Spill: 5"]
 
 
-def test_scratch_guard_covers_fp32_attention():
-    """The fp32 kernel of d = 128, which uses every register it may, is guarded too."""
+@pytest.mark.parametrize("source,name", [
+    # the fp32 attention of d = 128, which uses every register it may
+    ("attention.hip", "_ZN7omnimem12_GLOBAL__N_110k_attn_f32ILi128EEEvNS0_8AttnArgsE"),
+    # the probability scores of d = 64, whose registers are held to three workgroups a CU
+    ("prob.hip", "_ZN7omnimem12_GLOBAL__N_114k_prob_partialItLi64ELb1EEEvNS0_8ProbArgsE")])
+def test_scratch_guard_covers(source, name):
     from paper_2605_30519_amd import _build
 
-    name = "_ZN7omnimem12_GLOBAL__N_110k_attn_f32ILi128EEEvNS0_8AttnArgsE"
     spilled = f"x: remark: Function Name: {name} [-R]\nx: remark:     VGPRs Spill: 3 [-R]"
-    assert _build.scratch_users(spilled, _build.NO_SCRATCH["attention.hip"]) == [f"{name}: VGPRs Spill: 3"]
+    assert _build.scratch_users(spilled, _build.NO_SCRATCH[source]) == [f"{name}: VGPRs Spill: 3"]
