@@ -13,25 +13,36 @@ namespace {
 
 constexpr int kFuseThreads = 256;
 
+// 16 bytes to memory, PAST the caches or as usual.
+template <bool PAST>
+__device__ __forceinline__ void store16(u32x4 w, void* p) {
+  if constexpr (PAST)
+    __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+  else
+    *reinterpret_cast<u32x4*>(p) = w;
+}
+
 template <typename T>
 struct Chunk;
 
 template <>
 struct Chunk<uint16_t> {
   static constexpr int N = 8;
+  template <bool PAST>
   __device__ __forceinline__ static void store(uint16_t* p, const float (&x)[8]) {
     bf16x8 w;  // nearest even, two a conversion
 #pragma unroll
     for (int j = 0; j < 8; ++j) w[j] = static_cast<__bf16>(x[j]);
-    *reinterpret_cast<bf16x8*>(p) = w;
+    store16<PAST>(__builtin_bit_cast(u32x4, w), p);
   }
 };
 
 template <>
 struct Chunk<float> {
   static constexpr int N = 4;
+  template <bool PAST>
   __device__ __forceinline__ static void store(float* p, const float (&x)[4]) {
-    *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]);
+    store16<PAST>(__builtin_bit_cast(u32x4, f32x4{x[0], x[1], x[2], x[3]}), p);
   }
 };
 
@@ -40,17 +51,24 @@ struct Chunk<float> {
 // six loads are in flight before the first product.  Bound by its 4 tensors' bytes, from
 // HBM or, written just before, from the MALL.  One chunk per lane, the row found by a
 // 64-bit division and a branch's loads behind the one before: 4,680 rows x 12 heads, bf16,
-// d = 128: 12.0 -> 10.8 us; 8 heads 7.8 -> 6.4; fp32, 1,560 rows 7.0 -> 6.4.  Four chunks
-// per lane break the lines (11.0 us).  Nontemporal loads gain up to 7% when the branches
-// come from HBM and lose as much when they are still cached, as after their attention.
+// d = 128: 12.0 -> 10.8 us; 8 heads 7.8 -> 6.4; fp32, 1,560 rows 7.0 -> 4.9.  Four chunks
+// per lane break the lines (11.0 us).
+// The output is stored past the caches, which then hold more of the branches: 40 heads x
+// 4,680 rows, fp32 (383 MB) 69.5 -> 54.7 us, 32 heads 48.8 -> 43.9, smaller calls unchanged.
+// STREAM reads the branches past the caches instead and stores as usual.  That loses where
+// the branches are still there, as after their attention (40 heads, bf16, 192 MB: 28.5 ->
+// 32.9 us; the fp32 call of 383 MB 54.7 -> 59.7), and gains where they are more than the
+// 256 MB memory-side cache holds for long: 40 heads x 12,000 rows, bf16 (369 MB of branches)
+// 87.1 -> 75.9, 9,000 rows, fp32 (553 MB) 129 -> 111.
 constexpr int kFuseChunks = 2;
+constexpr int64_t kFuseStreamBytes = 320ll << 20;  // bytes of branches
 
 template <typename T, int D>
 constexpr int fuse_lanes() {  // lanes per row
   return D / Chunk<T>::N / kFuseChunks;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool STREAM>
 __global__ __launch_bounds__(kFuseThreads) void k_gated_combine(const T* __restrict__ o_cmp, const T* __restrict__ o_slc,
                                                                 const T* __restrict__ o_swa,
                                                                 const float* __restrict__ gate, int64_t rows, T* out) {
@@ -64,7 +82,10 @@ __global__ __launch_bounds__(kFuseThreads) void k_gated_combine(const T* __restr
   for (int c = 0; c < 3; ++c) {
     if (src[c] == nullptr) continue;
 #pragma unroll
-    for (int u = 0; u < kFuseChunks; ++u) raw[c][u] = *reinterpret_cast<const uint4*>(src[c] + at + u * LPR * N);
+    for (int u = 0; u < kFuseChunks; ++u) {
+      const T* p = src[c] + at + u * LPR * N;
+      raw[c][u] = STREAM ? load_once(p) : *reinterpret_cast<const uint4*>(p);
+    }
   }
   float logit[3];
 #pragma unroll
@@ -83,7 +104,7 @@ __global__ __launch_bounds__(kFuseThreads) void k_gated_combine(const T* __restr
     }
   }
 #pragma unroll
-  for (int u = 0; u < kFuseChunks; ++u) Chunk<T>::store(out + at + u * LPR * N, acc[u]);
+  for (int u = 0; u < kFuseChunks; ++u) Chunk<T>::template store<!STREAM>(out + at + u * LPR * N, acc[u]);
 }
 
 template <typename T, int D>
@@ -92,7 +113,9 @@ hipError_t launch_typed(int64_t rows, const void* o_cmp, const void* o_slc, cons
   constexpr int per = kFuseThreads / fuse_lanes<T, D>();  // rows per workgroup
   const int64_t blocks = (rows + per - 1) / per;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  return launch_kernel(k_gated_combine<T, D>, dim3(static_cast<unsigned>(blocks)), dim3(kFuseThreads), 0, stream,
+  const int branches = (o_cmp != nullptr) + (o_slc != nullptr) + (o_swa != nullptr);
+  const bool stream_in = branches * rows * D * static_cast<int64_t>(sizeof(T)) > kFuseStreamBytes;
+  return launch_kernel(stream_in ? k_gated_combine<T, D, true> : k_gated_combine<T, D, false>, dim3(static_cast<unsigned>(blocks)), dim3(kFuseThreads), 0, stream,
                        static_cast<const T*>(o_cmp), static_cast<const T*>(o_slc), static_cast<const T*>(o_swa), gate,
                        rows, static_cast<T*>(out));
 }

@@ -367,6 +367,23 @@ def test_gated_combine_rows(dev, dtype, d):
         assert torch.equal(full[1][rows:], behind)
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 128), (torch.float32, 64)])
+def test_gated_combine_streamed(dev, dtype, d):
+    """More than 320 MiB of branches are read past the caches: the same bits as calls over
+    parts of the rows, out of place and over a branch."""
+    rows = (320 << 20) // (3 * d * dtype.itemsize) + 77
+    say(f"gated combine rows={rows} d={d} {dtype}")
+    g = torch.Generator(device=dev).manual_seed(8)
+    branches = [torch.randn((rows, 1, d), generator=g, device=dev).to(dtype) for _ in range(3)]
+    logits = torch.randn((rows, 1, 3), generator=g, device=dev)
+    parts = torch.cat([omnimem_gated_combine(*[b[i:i + 200000] for b in branches], logits[i:i + 200000])
+                       for i in range(0, rows, 200000)])
+    assert torch.equal(omnimem_gated_combine(*branches, logits), parts)
+    omnimem_gated_combine(*branches, logits, out=branches[2])
+    torch.cuda.synchronize()
+    assert torch.equal(branches[2], parts)
+
+
 @pytest.mark.parametrize("top_k", [3, 70])
 def test_small_group_lists_past_count(dev, top_k):
     """The one-wave-per-group walk reads lists ahead of their counts: whatever stands past a
