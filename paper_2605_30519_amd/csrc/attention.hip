@@ -456,9 +456,10 @@ __device__ __forceinline__ float pair_sum(float v) {
 // ------------------------------------------------------------------ bf16 / MFMA, 32 rows per wave
 // d = 64, groups of more than 32 rows: 8 waves, two per SIMD, each own 32 query rows, and the
 // two of a SIMD run a tile half a step apart: waves 0-3 do QK(t), softmax(t), PV(t); waves
-// 4-7 PV(t-1), QK(t), softmax(t), so that one issues MFMAs while the other is in its softmax,
-// which bounds the tile (about 190 VALU operations a wave, 33 of them exponentials, for 16
-// MFMAs).
+// 4-7 PV(t-1), QK(t), softmax(t), so that one issues MFMAs while the other is in its softmax.
+// The softmax bounds it: of a SIMD's cycles VALU work issues for 64% (some 200 operations a
+// wave and tile, 33 of them exponentials), the MFMA pipe is busy for 32%, half of that under
+// the VALU work, and a fifth has neither.
 // The max of a row is the true one of the tiles so far, so a row's largest P is 1 and its
 // bf16 exact.  A max that lags, as the 64-row kernel's does, rounds the largest P like any
 // other: outputs 2.33e-3 off fp64 against 2.21e-3 (16 heads x 1,560 rows x 4,680 keys).
@@ -1470,8 +1471,9 @@ __global__ __launch_bounds__(kR64Waves* kWave, 1) void k_attn_bf16_r64(AttnArgs 
 //  - K of the next tile is on its way while the PV MFMAs of this one run, V while the next
 //    tile's QK MFMAs run: one copy of each.
 // Against one lane per query row with its dot products and exponentials in series, at
-// 12 heads x 1,560 rows x 1,024 keys, d = 128: 2,485 -> 117 us (82 TFLOP/s; 62 us at the
-// rate of a large fp32 product, 82 us for the CUs that get three of the 588 workgroups);
+// 12 heads x 1,560 rows x 1,024 keys, d = 128: 2,485 -> 114 us (84 TFLOP/s; 62 us at the
+// rate of a large fp32 product, 82 us for the CUs that get three of the 588 workgroups; the
+// MFMA pipe is busy for 73% of a busy CU's cycles);
 // at 2 heads x 256 rows x 256 keys, d = 64: 292 -> 11 us.
 constexpr int kF32Rows = 32;
 constexpr int kF32Keys = 32;
