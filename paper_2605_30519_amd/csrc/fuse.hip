@@ -115,7 +115,8 @@ hipError_t launch_typed(int64_t rows, const void* o_cmp, const void* o_slc, cons
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
   const int branches = (o_cmp != nullptr) + (o_slc != nullptr) + (o_swa != nullptr);
   const bool stream_in = branches * rows * D * static_cast<int64_t>(sizeof(T)) > kFuseStreamBytes;
-  return launch_kernel(stream_in ? k_gated_combine<T, D, true> : k_gated_combine<T, D, false>, dim3(static_cast<unsigned>(blocks)), dim3(kFuseThreads), 0, stream,
+  const auto kernel = stream_in ? k_gated_combine<T, D, true> : k_gated_combine<T, D, false>;
+  return launch_kernel(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kFuseThreads), 0, stream,
                        static_cast<const T*>(o_cmp), static_cast<const T*>(o_slc), static_cast<const T*>(o_swa), gate,
                        rows, static_cast<T*>(out));
 }

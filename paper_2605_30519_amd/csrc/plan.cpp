@@ -70,7 +70,8 @@ int attn_key_streams(int D, int64_t groups, int rows, int64_t tiles, int cus) {
   for (int ks = 1; ks <= (D == 128 ? 2 : 4); ks *= 2, ++cost) {
     const int per_wg = kAttnRows / ks;
     const int64_t rounds = (groups * ((rows + per_wg - 1) / per_wg) + cus - 1) / cus;
-    const double time = static_cast<double>(rounds) * (cost->start + static_cast<double>(cost->tile) * ((tiles + ks - 1) / ks));
+    const double tiles_time = static_cast<double>(cost->tile) * static_cast<double>((tiles + ks - 1) / ks);
+    const double time = static_cast<double>(rounds) * (cost->start + tiles_time);
     if (ks == 1 || time < least) {
       best = ks;
       least = time;
